@@ -5,6 +5,9 @@
 // x [T][K] bf16, W and W_N [N][K] bf16 (a linear layer's output-by-input
 // layout), y [T][N] fp32.
 //
+// Up to kSkinnyRows rows a weight-streaming kernel does the whole call.  More rows:
+// routing, then tiles.
+//
 // Routing: three small kernels lay the rows out as one permutation: the
 // non-Nexus rows in order, then the Nexus rows in order.  The GEMM then runs
 // over 128-row tiles of that permutation (a tile never mixes the two groups, so
@@ -237,6 +240,118 @@ __global__ __launch_bounds__(kPThreads) void routed_gemm_kernel(
     }
 }
 
+// Few rows (the tokens one generation step adds, a short turn's Nexus rows): the product
+// only streams the weights, so the kernel is built around that stream.  A workgroup owns
+// 16 NT output columns of one weight set for a block of 16 TT rows, and its NW waves a
+// contiguous part of K each.  A wave stages 64-deep slices of its weight and x rows into
+// an LDS ring of S slots of its own (direct-to-LDS loads, whole 128-byte row pieces), so
+// no barrier stands between the loads and the products.  The rows of a block are all
+// multiplied by the workgroup's set and those of its role are stored, so no permutation
+// is built and the call is one launch; a set without rows in the block costs its
+// workgroup one look at the roles.  The waves' partial sums are added in wave order.
+// Bound by the weights' stream: 8 rows of K = 4096, N = 6144 take 10.9 us (50 MB, 4.6 TB/s;
+// the tile kernel with its routing launches took 55), 64 rows 13.9 (58), 128 rows 20.8
+// (59), weights not in the Infinity Cache.  Loading the operand registers straight from
+// memory instead (16 rows per 16 lanes) took 16.7 us for 8 rows and 40 for 64: the address
+// path then handles one lane a cycle.
+constexpr int kSkinnyRows = 256;
+
+template <int NT, int TT, int NW, int S>
+__global__ __launch_bounds__(NW * kWave) void skinny_proj_kernel(
+    const uint16_t *__restrict__ x, const uint16_t *__restrict__ w_text, const uint16_t *__restrict__ w_nexus,
+    float *__restrict__ y, const uint8_t *__restrict__ role, int T, int K, int N, const int32_t *status) {
+  constexpr int C = 16 * NT, R = 16 * TT;         // columns and rows of the workgroup
+  constexpr int IN = (C + R) / 8;                 // direct-to-LDS instructions per slot (8 rows each)
+  constexpr int SLOT = (C + R) * kPK;             // elements per slot: weight rows, then x rows
+  constexpr int RS = C + 1;                       // row stride of the partial sums, in floats
+  static_assert((S - 1) * IN < 64, "the wait count fits vmcnt");
+  static_assert(NW * R * RS * sizeof(float) <= NW * S * SLOT * sizeof(uint16_t), "the partial sums fit in the ring");
+  __shared__ __align__(16) uint16_t ring[NW * S * SLOT];
+  const bool nexus = blockIdx.y != 0;
+  const int n0 = blockIdx.x * C, r0 = blockIdx.z * R;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const int lane = threadIdx.x % kWave;
+  // one round trip for the status word and the roles (every wave for itself: the same answer)
+  const int32_t pending = __hip_atomic_load(status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  static_assert(R <= 2 * kWave, "two roles per lane");
+  const bool m0 = (role[min(r0 + min(lane, R - 1), T - 1)] == kNexus) == nexus;   // rows past the end repeat one
+  const bool m1 = R > kWave && (role[min(r0 + min(lane + kWave, R - 1), T - 1)] == kNexus) == nexus;
+  if (pending != 0 || !__any(m0 || m1)) return;
+
+  const int nk = K / kPK;
+  const int per = (nk + NW - 1) / NW;
+  const int k0 = min(nk, wave * per);
+  const int steps = min(nk, k0 + per) - k0;
+  const char *wb = uniform_ptr(reinterpret_cast<const char *>(nexus ? w_nexus : w_text));
+  const char *xb = uniform_ptr(reinterpret_cast<const char *>(x));
+  // lane L of instruction i fills row 8 i + L / 8 at chunk position L % 8 (both operands
+  // lie below 4 GiB, checked by the host)
+  uint32_t off[IN];
+#pragma unroll
+  for (int i = 0; i < IN; ++i) {
+    const int r = 8 * i + lane / 8;
+    const int c = (lane % 8) ^ swz_p(r % 16);
+    const int row = i < C / 8 ? min(n0 + r, N - 1) : min(r0 + r - C, T - 1);
+    off[i] = static_cast<uint32_t>(row) * static_cast<uint32_t>(K) * 2u + 16u * static_cast<uint32_t>(c);
+  }
+  uint16_t *const my = ring + wave * S * SLOT;
+  const uint32_t my0 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(my));
+  auto issue = [&](int step, int slot) {
+    const size_t kb = static_cast<size_t>(k0 + step) * kPK * 2;
+#pragma unroll
+    for (int i = 0; i < IN; ++i)
+      dma_row16_s((i < C / 8 ? wb : xb) + kb, off[i], my0 + slot * (SLOT * 2) + i * kWave * 16);
+  };
+  const int fr = lane & 15, quarter = lane >> 4;   // fragment row; K chunk of the sub-step
+  f32x4 acc[NT][TT];
+#pragma unroll
+  for (int i = 0; i < NT; ++i)
+#pragma unroll
+    for (int t = 0; t < TT; ++t) acc[i][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+  for (int s = 0; s < min(S, steps); ++s) issue(s, s);
+  for (int s = 0, slot = 0; s < steps; ++s, slot = slot + 1 == S ? 0 : slot + 1) {
+    if (s + S <= steps) wait_vm<(S - 1) * IN>();   // all but the slots behind this one
+    else wait_vm<0>();
+    const uint16_t *sl = my + slot * SLOT;
+#pragma unroll
+    for (int kk = 0; kk < kPK / 32; ++kk) {
+      const int p = ((4 * kk + quarter) ^ swz_p(fr)) * 8;
+      bf16x8 wf[NT], xf[TT];
+#pragma unroll
+      for (int i = 0; i < NT; ++i) wf[i] = *reinterpret_cast<const bf16x8 *>(&sl[(16 * i + fr) * kPK + p]);
+#pragma unroll
+      for (int t = 0; t < TT; ++t) xf[t] = *reinterpret_cast<const bf16x8 *>(&sl[(C + 16 * t + fr) * kPK + p]);
+#pragma unroll
+      for (int t = 0; t < TT; ++t)
+#pragma unroll
+        for (int i = 0; i < NT; ++i)
+          acc[i][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[i], xf[t], acc[i][t], 0, 0, 0);
+    }
+    __builtin_amdgcn_s_waitcnt(15 | (3 << 14) | (7 << 4));   // lgkmcnt(0): the slot may be refilled
+    if (s + S < steps) issue(s + S, slot);
+  }
+  __syncthreads();   // every wave is done with its part of the ring (and its loads have landed)
+  // lane (fr, quarter) holds columns 16 i + 4 quarter .. + 3 of row 16 t + fr
+  float *red = reinterpret_cast<float *>(ring);
+#pragma unroll
+  for (int i = 0; i < NT; ++i)
+#pragma unroll
+    for (int t = 0; t < TT; ++t)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) red[(wave * R + 16 * t + fr) * RS + 16 * i + 4 * quarter + e] = acc[i][t][e];
+  __syncthreads();
+  for (int u = threadIdx.x; u < R * C; u += NW * kWave) {
+    const int r = u / C, c = u % C;
+    if (r0 + r < T && n0 + c < N && (role[r0 + r] == kNexus) == nexus) {
+      float v = red[r * RS + c];
+#pragma unroll
+      for (int w = 1; w < NW; ++w) v += red[(w * R + r) * RS + c];
+      y[static_cast<size_t>(r0 + r) * N + n0 + c] = v;
+    }
+  }
+}
+
 int routed_gemm_blocks(int T, int N) {
   const int m_tiles = (T + kPM - 1) / kPM + 1;   // the two groups can each end in a partial tile
   const int n_tiles = (N + kPN - 1) / kPN;
@@ -247,6 +362,30 @@ int routed_gemm_blocks(int T, int N) {
 hipError_t launch_routed_gemm(int T, int K, int N, const uint8_t *role, const uint16_t *x, const uint16_t *w_text,
                               const uint16_t *w_nexus, float *y, int32_t *blk_nexus, int32_t *counts, int32_t *perm,
                               int32_t *status, hipStream_t stream) {
+  if (T <= kSkinnyRows) {
+#define SKINNY(NT, TT, NW, S)                                                                               \
+  skinny_proj_kernel<NT, TT, NW, S>                                                                         \
+      <<<dim3((N + 16 * NT - 1) / (16 * NT), 2, (T + 16 * TT - 1) / (16 * TT)), dim3(NW * kWave), 0, stream>>>( \
+          x, w_text, w_nexus, y, role, T, K, N, status)
+    // Two column blocks a workgroup halve the x rows it stages per weight row, one keeps
+    // more workgroups busy: N = 6144, 64 rows 13.9 us with two and 19.3 with one; N = 4096,
+    // 13.0 and 11.6; up to 16 rows one is faster at every size.  More than 128 rows stage
+    // enough x to want two everywhere (256 rows, N = 4096: 21 and 32).
+    const bool two = (N + 15) / 16 > 256 || T > 128;
+    if (T <= 16) SKINNY(1, 1, 8, 2);
+    else if (T <= 32) {
+      if (two) SKINNY(2, 2, 8, 2);
+      else SKINNY(1, 2, 8, 3);
+    } else if (T <= 64) {
+      if (two) SKINNY(2, 4, 4, 3);
+      else SKINNY(1, 4, 4, 3);
+    } else {
+      if (two) SKINNY(2, 8, 4, 2);
+      else SKINNY(1, 8, 4, 2);
+    }
+#undef SKINNY
+    return hipGetLastError();
+  }
   const int nblk = (T + kRouteThreads - 1) / kRouteThreads;
   route_count_kernel<<<dim3(nblk), dim3(kRouteThreads), 0, stream>>>(role, T, blk_nexus, status);
   route_scan_kernel<<<dim3(1), dim3(kRouteThreads), 0, stream>>>(nblk, T, blk_nexus, counts, status);

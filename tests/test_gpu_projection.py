@@ -127,3 +127,30 @@ def test_projection_argument_errors():
     x = torch.zeros((10, 64), dtype=torch.bfloat16, device="cuda")
     w = torch.zeros((8, 64), dtype=torch.bfloat16, device="cuda")
     assert sonic.role_projection(role, x, w, w, y, ws[:16], st0) == sonic.ERR_WORKSPACE
+
+
+@pytest.mark.parametrize("T,K,N", [(1, 4096, 33), (16, 64, 16), (17, 640, 100), (32, 64, 4113), (33, 128, 70),
+                                   (64, 1088, 4112), (65, 64, 17), (128, 192, 31), (129, 320, 33), (256, 512, 150),
+                                   (257, 64, 129), (511, 128, 127)])
+def test_projection_dispatch_edges(T, K, N):
+    """Row counts on either side of every edge of the kernels' row blocks, K shorter than a
+    wave's share and odd column counts, with alternating and with uniform roles."""
+    rng = np.random.default_rng(3 * T + K + N)
+    x, wt, wn = _bits(rng, (T, K)), _bits(rng, (N, K), 0.05), _bits(rng, (N, K), 0.05)
+    for role in (np.where(np.arange(T) % 3 == 0, OL.NEXUS, OL.CURRENT).astype(np.uint8),
+                 np.full(T, OL.CURRENT, np.uint8), np.full(T, OL.NEXUS, np.uint8)):
+        check(run(role, x, wt, wn), role, x, wt, wn, f"T={T} K={K} N={N}")
+
+
+@pytest.mark.parametrize("T,N", [(8, 300), (600, 300)])
+def test_projection_pending_status_writes_nothing(T, N):
+    H.need_gpu()
+    y = torch.full((T, N), 7.0, dtype=torch.float32, device="cuda")
+    ws = torch.empty(sonic.role_projection_workspace_bytes(T), dtype=torch.uint8, device="cuda")
+    status = torch.full((1,), sonic.ERR_BAD_LAYOUT, dtype=torch.int32, device="cuda")
+    role = torch.full((T,), int(OL.CURRENT), dtype=torch.uint8, device="cuda")
+    x = torch.ones((T, 64), dtype=torch.bfloat16, device="cuda")
+    w = torch.ones((N, 64), dtype=torch.bfloat16, device="cuda")
+    assert sonic.role_projection(role, x, w, w, y, ws, status) == sonic.OK
+    torch.cuda.synchronize()
+    assert bool((y == 7.0).all()) and int(status.item()) == sonic.ERR_BAD_LAYOUT

@@ -5,42 +5,35 @@
 // x [T][K] bf16, W and W_N [N][K] bf16 (a linear layer's output-by-input
 // layout), y [T][N] fp32.
 //
-// Up to kSkinnyRows rows a weight-streaming kernel does the whole call.  More rows:
-// routing, then tiles.
+// Few rows go to a weight-streaming kernel that does the whole call; more rows are laid
+// out as one permutation, the non-Nexus rows in order, then the Nexus rows in order, and
+// multiplied in tiles of it (a tile never mixes the two groups, so each tile reads one
+// weight set), gathering x rows through the permutation and scattering y rows back.
+// Up to kLocalRows rows every tile's workgroup ranks the rows itself; more rows take
+// three small routing kernels first.
 //
-// Routing: three small kernels lay the rows out as one permutation: the
-// non-Nexus rows in order, then the Nexus rows in order.  The GEMM then runs
-// over 128-row tiles of that permutation (a tile never mixes the two groups, so
-// each tile reads one weight set), gathering its x rows through the
-// permutation and scattering its y rows back.
-//
-// GEMM: 128 x 256 output tile per workgroup of eight waves, each wave a 64 x 64
-// part as 2 x 2 blocks of v_mfma_f32_32x32x16_bf16, K in steps of 64.  Both
-// operands are K-contiguous rows (x rows and weight rows), staged straight from
-// global memory into LDS (direct-to-LDS loads), double-buffered: step s + 1
-// streams in while step s is multiplied.  LDS rows are 128 bytes with an XOR
-// swizzle on the 16-byte chunk index, so the fragment reads (32 rows at one
-// chunk) are bank-conflict free.  Each fragment read feeds two MFMAs, and the
-// reads are scheduled two K sub-steps ahead of the MFMAs that consume them.
-// Tiles are laid out so that the workgroups of one XCD share a band of output
-// columns and walk the row tiles in order: the x rows a tile needs are also
-// needed by the tiles of the other columns of the band, resident on the same
-// XCD at the same time, and so is each weight chunk, which keeps both in its L2.
+// GEMM: PM x PN output tile per workgroup of eight waves (2 x 4 parts), in blocks of
+// v_mfma_f32_16x16x32_bf16, K in steps of 64.  Both operands are K-contiguous rows (x
+// rows and weight rows), staged straight from global memory into an LDS ring of S steps
+// (direct-to-LDS loads).  LDS rows are 128 bytes with an XOR swizzle on the 16-byte
+// chunk index, so the fragment reads (16 rows at one chunk) are bank-conflict free.
+// Tiles are laid out so that the workgroups of one XCD share a band of output columns
+// and walk its row tiles in order: the x rows a tile needs are also needed by the tiles
+// of the other columns of the band, resident on the same XCD at the same time, and so is
+// each weight chunk, which keeps both in its L2.
 #include "common.h"
 #include "scan.h"
+
+#include <algorithm>
+#include <cmath>
+#include <type_traits>
 
 namespace sonic {
 
 constexpr int kRouteThreads = 1024;
-// 128 x 256 tiles, eight waves as 2 (rows) x 4 (columns), each 64 x 64.  Measured on
-// the 8B-shaped QKV product (T = 43392, K = 4096, N = 6144): 128 x 128 with four waves
-// 0.80-0.88 PFLOP/s, 256 x 128 0.91, 128 x 256 0.93; 256 x 256 tiles need more than
-// 256 registers per lane and spill.
-constexpr int kPM = 128, kPN = 256, kPK = 64;    // tile rows, tile columns, K step
+constexpr int kPK = 64;                          // K step
 constexpr int kPWavesM = 2, kPWavesN = 4;        // waves along rows and columns
 constexpr int kPThreads = kPWavesM * kPWavesN * kWave;
-constexpr int kPBM = kPM / kPWavesM / 32, kPBN = kPN / kPWavesN / 32;   // 32x32 blocks per wave
-constexpr int kPRowChunks = kPK / 8;            // 16-byte chunks per staged row
 
 // Pass 1: Nexus rows per block of 1024 rows.
 __global__ __launch_bounds__(kRouteThreads) void route_count_kernel(const uint8_t *__restrict__ role, int T,
@@ -98,33 +91,105 @@ __global__ __launch_bounds__(kRouteThreads) void route_fill_kernel(const uint8_t
 // chunk position of chunk c in staged row r (16 rows hit 16 distinct 4-bank groups)
 __device__ __forceinline__ int swz_p(int r) { return (r & 7) ^ ((r >> 3) & 1); }
 
-__global__ __launch_bounds__(kPThreads) void routed_gemm_kernel(
-    const uint16_t *__restrict__ x, const uint16_t *__restrict__ w_text, const uint16_t *__restrict__ w_nexus,
-    float *__restrict__ y, const int32_t *__restrict__ perm, const int32_t *__restrict__ counts, int K, int N,
-    int n_tiles, int band) {
-  __shared__ __align__(16) uint16_t a_lds0[kPM * kPK];
-  __shared__ __align__(16) uint16_t a_lds1[kPM * kPK];
-  __shared__ __align__(16) uint16_t b_lds0[kPN * kPK];
-  __shared__ __align__(16) uint16_t b_lds1[kPN * kPK];
-  __shared__ int rows_lds[kPM];
+// Routing inside a tile's workgroup, for up to kLocalRows rows: every workgroup reads all
+// roles and ranks the rows itself, which saves the three routing launches.  Bit j of
+// flags: row 512 j + thread is a Nexus row; before[j]: Nexus rows before it.
+constexpr int kLocalRounds = 16;
+constexpr int kLocalRows = kLocalRounds * kPThreads;
+__device__ __forceinline__ bool local_routes(const uint8_t *__restrict__ role, int T, const int32_t *status, int &flags,
+                                             int (&before)[kLocalRounds], int &total) {
+  constexpr int NW = kPThreads / kWave;
+  static_assert(kLocalRounds * NW == 2 * kWave, "two counts per lane");
+  __shared__ int cnt[2 * kWave];
+  const int32_t pending = __hip_atomic_load(status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
+  uint8_t mine[kLocalRounds];
+#pragma unroll
+  for (int j = 0; j < kLocalRounds; ++j) {
+    mine[j] = kText;
+    if (j * kPThreads < T) mine[j] = role[min(j * kPThreads + static_cast<int>(threadIdx.x), T - 1)];
+  }
+  if (pending != 0) return false;   // nothing raises the status in this call: the same answer in every wave
+#pragma unroll
+  for (int j = 0; j < kLocalRounds; ++j) {
+    const bool nx = j * kPThreads + threadIdx.x < T && mine[j] == kNexus;
+    flags |= (nx ? 1 : 0) << j;
+    const uint64_t m = __ballot(nx);
+    before[j] = lanes_below(m);
+    if (lane == 0) cnt[j * NW + wave] = __popcll(m);
+  }
+  __syncthreads();
+  // every wave scans the 128 counts: lane l holds counts 2l and 2l + 1
+  const int c0 = cnt[2 * lane], c1 = cnt[2 * lane + 1];
+  int incl = c0 + c1;
+#pragma unroll
+  for (int o = 1; o < kWave; o <<= 1) {
+    const int v = __shfl_up(incl, o);
+    if (lane >= o) incl += v;
+  }
+  const int ex = incl - c0 - c1;
+#pragma unroll
+  for (int j = 0; j < kLocalRounds; ++j) {
+    const int i = j * NW + wave;
+    before[j] += __shfl(ex, i / 2) + ((i & 1) ? __shfl(c0, i / 2) : 0);
+  }
+  total = __shfl(incl, kWave - 1);
+  return true;
+}
 
-  // tile of this workgroup: XCD x takes column tiles [x * band, (x + 1) * band), row tiles in order
+// The matrix cores bound a large tile (T = 43392, K = 4096, N = 6144: 1.82 ms, 1.20
+// PFLOP/s, where 128 x 256 tiles with two barriers a step took 2.19 ms), the LDS reads
+// come next: a 128 x 64 part per wave reads 0.75 KB of fragments per 32 Kflop product, a
+// 64 x 64 one 1 KB, which is all the LDS delivers in that time.  Blocks of 16 x 16 keep
+// the accumulators in four-register groups; 32 x 32 blocks of this part spilled.  A small
+// tile is bound by the latency of its steps (about 1.5 us each with one in flight), so
+// its ring is deeper.
+template <int PM, int PN, int S, bool LOCAL>
+__global__ __launch_bounds__(kPThreads, 2) void routed_gemm_kernel(
+    const uint16_t *__restrict__ x, const uint16_t *__restrict__ w_text, const uint16_t *__restrict__ w_nexus,
+    float *__restrict__ y, const uint8_t *__restrict__ role, const int32_t *__restrict__ perm,
+    const int32_t *__restrict__ counts, int T, int K, int N, int n_tiles, int xn, int band, const int32_t *status) {
+  constexpr int BM = PM / kPWavesM / 16, BN = PN / kPWavesN / 16;   // 16 x 16 blocks per wave
+  __shared__ __align__(16) uint16_t a_lds[S][PM * kPK];
+  __shared__ __align__(16) uint16_t b_lds[S][PN * kPK];
+  __shared__ int rows_lds[PM];
+
+  // tile of this workgroup: the XCDs form (8 / xn) x xn bands; a band takes `band` column
+  // tiles and every (8 / xn)-th row tile, in order
   const int xcd = blockIdx.x % kNumXcd;
   const int loc = blockIdx.x / kNumXcd;
-  const int m_tile = loc / band;
-  const int n_tile = xcd * band + loc % band;
-  const int n_text = counts[0], n_nexus = counts[1];
-  const int mt_text = (n_text + kPM - 1) / kPM;
-  const int mt_all = mt_text + (n_nexus + kPM - 1) / kPM;
-  if (n_tile >= n_tiles || m_tile >= mt_all) return;
+  const int m_tile = loc / band * (kNumXcd / xn) + xcd / xn;
+  const int n_tile = xcd % xn * band + loc % band;
+  if (n_tile >= n_tiles) return;
+  int n_text, n_nexus, flags = 0, before[LOCAL ? kLocalRounds : 1];
+  if constexpr (LOCAL) {
+    if (!local_routes(role, T, status, flags, before, n_nexus)) return;
+    n_text = T - n_nexus;
+  } else {
+    n_text = counts[0];
+    n_nexus = counts[1];
+  }
+  const int mt_text = (n_text + PM - 1) / PM;
+  const int mt_all = mt_text + (n_nexus + PM - 1) / PM;
+  if (m_tile >= mt_all) return;
   const bool nexus = m_tile >= mt_text;
-  const int g0 = nexus ? n_text : 0;                           // first slot of the group
-  const int row0 = (nexus ? m_tile - mt_text : m_tile) * kPM;  // first row of the tile in the group
-  const int nrows = min(kPM, (nexus ? n_nexus : n_text) - row0);
-  const int n0 = n_tile * kPN;
+  const int g0 = nexus ? n_text : 0;                          // first slot of the group
+  const int row0 = (nexus ? m_tile - mt_text : m_tile) * PM;  // first row of the tile in the group
+  const int nrows = min(PM, (nexus ? n_nexus : n_text) - row0);
+  const int n0 = n_tile * PN;
   const uint16_t *__restrict__ w = nexus ? w_nexus : w_text;
 
-  for (int r = threadIdx.x; r < kPM; r += kPThreads) rows_lds[r] = perm[g0 + row0 + min(r, nrows - 1)];
+  if constexpr (LOCAL) {
+#pragma unroll
+    for (int j = 0; j < kLocalRounds; ++j) {
+      const int row = j * kPThreads + threadIdx.x;
+      const bool nx = (flags >> j) & 1;
+      const int slot = (nx ? before[j] : row - before[j]) - row0;
+      if (row < T && nx == nexus && slot >= 0 && slot < PM) rows_lds[slot] = row;
+    }
+  } else {
+    for (int r = threadIdx.x; r < nrows; r += kPThreads) rows_lds[r] = perm[g0 + row0 + r];
+  }
   __syncthreads();
 
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
@@ -132,8 +197,9 @@ __global__ __launch_bounds__(kPThreads) void routed_gemm_kernel(
   // staging: instruction i of a tile fills rows 8i .. 8i + 7 (lane L: row 8i + L / 8 at
   // chunk position L % 8); wave w issues instructions w * IA .. of A and w * IB .. of B
   constexpr int kNW = kPThreads / kWave;
-  constexpr int IA = kPM / 8 / kNW, IB = kPN / 8 / kNW;   // per wave and step
-  static_assert(IA * kNW * 8 == kPM && IB * kNW * 8 == kPN, "whole instructions per wave");
+  constexpr int IA = PM / 8 / kNW, IB = PN / 8 / kNW;   // per wave and step
+  static_assert((S - 1) * (IA + IB) < 64, "the wait count fits vmcnt");
+  static_assert(IA * kNW * 8 == PM && IB * kNW * 8 == PN, "whole instructions per wave");
   // per-lane byte offsets from the operand bases (the host checks that both operands
   // lie below 4 GiB), with the K step added to the wave-uniform base
   uint32_t a_off[IA], b_off[IB];
@@ -141,7 +207,7 @@ __global__ __launch_bounds__(kPThreads) void routed_gemm_kernel(
   for (int q = 0; q < IA; ++q) {
     const int r = 8 * (wave * IA + q) + lane / 8;
     const int c = (lane % 8) ^ swz_p(r);
-    a_off[q] = static_cast<uint32_t>(rows_lds[r]) * static_cast<uint32_t>(K) * 2u + 16u * static_cast<uint32_t>(c);
+    a_off[q] = static_cast<uint32_t>(rows_lds[min(r, nrows - 1)]) * static_cast<uint32_t>(K) * 2u + 16u * static_cast<uint32_t>(c);
   }
 #pragma unroll
   for (int q = 0; q < IB; ++q) {
@@ -162,82 +228,109 @@ __global__ __launch_bounds__(kPThreads) void routed_gemm_kernel(
     for (int q = 0; q < IB; ++q) dma_row16_s(wb + koff, b_off[q], lb + (wave * IB + q) * kWave * 16);
   };
 
-  // this wave's (32 kPBM) x (32 kPBN) part of the tile
-  const int wm = 32 * kPBM * (wave % kPWavesM), wn = 32 * kPBN * (wave / kPWavesM);
-  const int li = lane & 31, lg = lane >> 5;
-  f32x16 acc[kPBM][kPBN];
+  // this wave's (16 BM) x (16 BN) part of the tile.  The products are W . x^T, so a lane
+  // ends up with four consecutive output columns of one row.
+  const int wm = 16 * BM * (wave % kPWavesM), wn = 16 * BN * (wave / kPWavesM);
+  const int fr = lane & 15, quarter = lane >> 4;   // fragment row; K chunk of the sub-step
+  f32x4 acc[BM][BN];
 #pragma unroll
-  for (int bi = 0; bi < kPBM; ++bi)
+  for (int i = 0; i < BM; ++i)
 #pragma unroll
-    for (int bj = 0; bj < kPBN; ++bj) acc[bi][bj] = f32x16{};
+    for (int j = 0; j < BN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-  // each A fragment feeds kPBN MFMAs, each B fragment kPBM
-  auto mult = [&](const uint16_t *a_buf, const uint16_t *b_buf) {
+  // A step of 64 is four phases: K sub-step (32 deep) by half of the wave's rows.  A
+  // phase's products run while the next phase's fragments are read into the other set
+  // (the weight fragments change every other phase).  Rows 16 apart share their
+  // swizzle, so the reads of a phase are one address per operand and immediates.
+  constexpr int H = BM / 2;
+  bf16x8 af[2][H], bf[2][BN];
+  const uint16_t *const a_rd = &a_lds[0][(wm + fr) * kPK];
+  const uint16_t *const b_rd = &b_lds[0][(wn + fr) * kPK];
+  const int ch[2] = {(quarter ^ swz_p(fr)) * 8, ((4 + quarter) ^ swz_p(fr)) * 8};
+  auto read_a = [&](int set, int buf, int kk, int half) {
 #pragma unroll
-    for (int kk = 0; kk < kPK / 16; ++kk) {
-      const int c = 2 * kk + lg;
-      bf16x8 af[kPBM], bf[kPBN];
-#pragma unroll
-      for (int t = 0; t < kPBM; ++t) {
-        const int ra = wm + 32 * t + li;
-        af[t] = *reinterpret_cast<const bf16x8 *>(&a_buf[(ra * kPRowChunks + (c ^ swz_p(ra))) * 8]);
-      }
-#pragma unroll
-      for (int t = 0; t < kPBN; ++t) {
-        const int rb = wn + 32 * t + li;
-        bf[t] = *reinterpret_cast<const bf16x8 *>(&b_buf[(rb * kPRowChunks + (c ^ swz_p(rb))) * 8]);
-      }
-#pragma unroll
-      for (int bi = 0; bi < kPBM; ++bi)
-#pragma unroll
-        for (int bj = 0; bj < kPBN; ++bj)
-          acc[bi][bj] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[bi], bf[bj], acc[bi][bj], 0, 0, 0);
-    }
-    // the fragment reads run two K sub-steps (eight reads) ahead of the MFMAs
-    order_reads_ahead<(kPK / 16) * kPBM * kPBN, 1, 2 * (kPBM + kPBN)>();
+    for (int t = 0; t < H; ++t)
+      af[set][t] = *reinterpret_cast<const bf16x8 *>(a_rd + ch[kk] + buf * PM * kPK + 16 * (half * H + t) * kPK);
   };
-
-  // double buffer: each wave issues IA + IB loads per step, so "step s has landed"
-  // is "all but the IA + IB most recent" while step s + 1 streams
+  auto read_b = [&](int buf, int kk) {
+#pragma unroll
+    for (int t = 0; t < BN; ++t)
+      bf[kk][t] = *reinterpret_cast<const bf16x8 *>(b_rd + ch[kk] + buf * PN * kPK + 16 * t * kPK);
+  };
+  // (products first: the other wave of the SIMD issues its reads and loads in between; 0.7 %)
+  auto mult = [&](int set, int kk, int half) {
+    __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+    for (int i = 0; i < H; ++i)
+#pragma unroll
+      for (int j = 0; j < BN; ++j)
+        acc[half * H + i][j] =
+            __builtin_amdgcn_mfma_f32_16x16x32_bf16(bf[kk][j], af[set][i], acc[half * H + i][j], 0, 0, 0);
+    __builtin_amdgcn_s_setprio(0);
+  };
+  // Behind the last read of a buffer comes the step's only barrier: every wave has its
+  // fragments of this buffer, so it is refilled (step s + S), and step s + 1 has landed
+  // in the next one, whose first fragments are read under the last products.
   const int steps = K / kPK;
-  stage(0, a_lds0, b_lds0);
-  for (int s = 0; s < steps; s += 2) {
-    if (s + 1 < steps) {
-      stage(s + 1, a_lds1, b_lds1);
-      wait_vm<IA + IB>();
-    } else {
-      wait_vm<0>();
-    }
-    lds_barrier();            // step s is in buffer 0 for every wave
-    mult(a_lds0, b_lds0);
-    lds_barrier();            // every wave is done with buffer 0
-    if (s + 1 >= steps) break;
-    if (s + 2 < steps) {
-      stage(s + 2, a_lds0, b_lds0);
-      wait_vm<IA + IB>();
-    } else {
-      wait_vm<0>();
-    }
-    lds_barrier();            // step s + 1 is in buffer 1
-    mult(a_lds1, b_lds1);
-    lds_barrier();            // every wave is done with buffer 1
+  auto phase_order = [&](auto reads) {
+    __builtin_amdgcn_sched_group_barrier(0x100, decltype(reads)::value, 0);   // DS reads
+    __builtin_amdgcn_sched_group_barrier(0x008, H * BN, 0);                   // MFMAs
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  auto step = [&](int s, int buf, int nxt) {
+    read_a(1, buf, 0, 1);
+    mult(0, 0, 0);
+    phase_order(std::integral_constant<int, H>{});
+    read_a(0, buf, 1, 0);
+    read_b(buf, 1);
+    mult(1, 0, 1);
+    phase_order(std::integral_constant<int, H + BN>{});
+    read_a(1, buf, 1, 1);
+    mult(0, 1, 0);
+    phase_order(std::integral_constant<int, H>{});
+    if (S > 2 && s + S <= steps) wait_vm<(S - 2) * (IA + IB)>();   // all but the steps behind s + 1
+    else wait_vm<0>();
+    lds_barrier();
+    read_a(0, nxt, 0, 0);   // past the last step: stale rows, never multiplied
+    read_b(nxt, 0);
+    __builtin_amdgcn_sched_barrier(0);
+    if (s + S < steps) stage(s + S, &a_lds[0][buf * PM * kPK], &b_lds[0][buf * PN * kPK]);
+    mult(1, 1, 1);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  for (int s = 0; s < min(S, steps); ++s) stage(s, a_lds[s], b_lds[s]);
+  if (steps >= S) wait_vm<(S - 1) * (IA + IB)>();
+  else wait_vm<0>();
+  lds_barrier();
+  read_a(0, 0, 0, 0);
+  read_b(0, 0);
+  // one step per round, the buffer an index: with the steps unrolled by the ring and an
+  // exit between them the compiler copies the accumulators and spills
+  for (int s = 0, buf = 0; s < steps; ++s) {
+    const int nxt = buf + 1 == S ? 0 : buf + 1;
+    step(s, buf, nxt);
+    buf = nxt;
   }
 
-  // lane (j = li, half lg) holds rows 8 (e / 4) + 4 lg + e % 4 of column j of each block
+  // lane (fr, quarter) holds columns 16 j + 4 quarter .. + 3 of row 16 i + fr
+  typedef f32x4 f32x4_u __attribute__((aligned(4)));   // y is 4-byte aligned, N any number
 #pragma unroll
-  for (int bi = 0; bi < kPBM; ++bi)
+  for (int i = 0; i < BM; ++i) {
+    const int r = wm + 16 * i + fr;
+    if (r >= nrows) continue;
+    float *yrow = y + static_cast<size_t>(rows_lds[r]) * N;
 #pragma unroll
-    for (int e = 0; e < 16; ++e) {
-      const int r = wm + 32 * bi + 8 * (e >> 2) + 4 * lg + (e & 3);
-      if (r < nrows) {
-        float *yrow = y + static_cast<size_t>(rows_lds[r]) * N;
+    for (int j = 0; j < BN; ++j) {
+      const int n = n0 + wn + 16 * j + 4 * quarter;
+      if (n + 4 <= N) {
+        *reinterpret_cast<f32x4_u *>(yrow + n) = acc[i][j];
+      } else {
 #pragma unroll
-        for (int bj = 0; bj < kPBN; ++bj) {
-          const int n = n0 + wn + 32 * bj + li;
-          if (n < N) yrow[n] = acc[bi][bj][e];
-        }
+        for (int e = 0; e < 4; ++e)
+          if (n + e < N) yrow[n + e] = acc[i][j][e];
       }
     }
+  }
 }
 
 // Few rows (the tokens one generation step adds, a short turn's Nexus rows): the product
@@ -352,17 +445,30 @@ __global__ __launch_bounds__(NW * kWave) void skinny_proj_kernel(
   }
 }
 
-int routed_gemm_blocks(int T, int N) {
-  const int m_tiles = (T + kPM - 1) / kPM + 1;   // the two groups can each end in a partial tile
-  const int n_tiles = (N + kPN - 1) / kPN;
-  const int band = (n_tiles + kNumXcd - 1) / kNumXcd;
-  return kNumXcd * band * m_tiles;
+template <int PM, int PN, int S, bool LOCAL>
+static void launch_tiles(int T, int K, int N, const uint8_t *role, const uint16_t *x, const uint16_t *w_text,
+                         const uint16_t *w_nexus, float *y, const int32_t *counts, const int32_t *perm,
+                         const int32_t *status, hipStream_t stream) {
+  const int m_tiles = (T + PM - 1) / PM + 1;   // the two groups can each end in a partial tile
+  const int n_tiles = (N + PN - 1) / PN;
+  // column bands: as many XCDs side by side as leave the fewest of them without columns
+  int xn = kNumXcd, band = (n_tiles + kNumXcd - 1) / kNumXcd;
+  for (int c = kNumXcd / 2; c >= 1; c /= 2) {
+    const int w = (n_tiles + c - 1) / c;
+    if (c * w < xn * band) xn = c, band = w;
+  }
+  const int m_per = (m_tiles + kNumXcd / xn - 1) / (kNumXcd / xn);
+  routed_gemm_kernel<PM, PN, S, LOCAL><<<dim3(kNumXcd * band * m_per), dim3(kPThreads), 0, stream>>>(
+      x, w_text, w_nexus, y, role, perm, counts, T, K, N, n_tiles, xn, band, status);
 }
 
 hipError_t launch_routed_gemm(int T, int K, int N, const uint8_t *role, const uint16_t *x, const uint16_t *w_text,
                               const uint16_t *w_nexus, float *y, int32_t *blk_nexus, int32_t *counts, int32_t *perm,
                               int32_t *status, hipStream_t stream) {
-  if (T <= kSkinnyRows) {
+  // The weight-streaming kernel reads the weights once per 128 rows, the tiles spread them
+  // over fewer workgroups: 256 rows of K = 4096 take 22.0 us streamed and 22.5 tiled for
+  // N = 4096, 39 and 28 for N = 6144; 128 rows 20.5 and 20.9, N = 6144.
+  if (T <= kSkinnyRows && (T <= 128 || N <= 4096)) {
 #define SKINNY(NT, TT, NW, S)                                                                               \
   skinny_proj_kernel<NT, TT, NW, S>                                                                         \
       <<<dim3((N + 16 * NT - 1) / (16 * NT), 2, (T + 16 * TT - 1) / (16 * TT)), dim3(NW * kWave), 0, stream>>>( \
@@ -386,16 +492,43 @@ hipError_t launch_routed_gemm(int T, int K, int N, const uint8_t *role, const ui
 #undef SKINNY
     return hipGetLastError();
   }
-  const int nblk = (T + kRouteThreads - 1) / kRouteThreads;
-  route_count_kernel<<<dim3(nblk), dim3(kRouteThreads), 0, stream>>>(role, T, blk_nexus, status);
-  route_scan_kernel<<<dim3(1), dim3(kRouteThreads), 0, stream>>>(nblk, T, blk_nexus, counts, status);
-  route_fill_kernel<<<dim3(nblk), dim3(kRouteThreads), 0, stream>>>(role, T, blk_nexus, counts, perm, status);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  const int n_tiles = (N + kPN - 1) / kPN;
-  const int band = (n_tiles + kNumXcd - 1) / kNumXcd;
-  routed_gemm_kernel<<<dim3(routed_gemm_blocks(T, N)), dim3(kPThreads), 0, stream>>>(
-      x, w_text, w_nexus, y, perm, counts, K, N, n_tiles, band);
+  const bool local = T <= kLocalRows;
+  if (!local) {
+    const int nblk = (T + kRouteThreads - 1) / kRouteThreads;
+    route_count_kernel<<<dim3(nblk), dim3(kRouteThreads), 0, stream>>>(role, T, blk_nexus, status);
+    route_scan_kernel<<<dim3(1), dim3(kRouteThreads), 0, stream>>>(nblk, T, blk_nexus, counts, status);
+    route_fill_kernel<<<dim3(nblk), dim3(kRouteThreads), 0, stream>>>(role, T, blk_nexus, counts, perm, status);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+#define TILES(PM, PN, S)                                                                                        \
+  (local ? launch_tiles<PM, PN, S, true>(T, K, N, role, x, w_text, w_nexus, y, counts, perm, status, stream)    \
+         : launch_tiles<PM, PN, S, false>(T, K, N, role, x, w_text, w_nexus, y, counts, perm, status, stream))
+  // Tile shape: large tiles read less per product, small ones keep 256 CUs busy and end
+  // with less waste.  A shape's cost is its time for one tile per CU (measured, K = 4096:
+  // 256 x 256 93 us, 128 x 256 58, 128 x 128 36, 64 x 128 43 for two, 64 x 64 29 for two
+  // and 20 alone) times the rounds it takes; a last, partial round runs faster than a
+  // full one and counts half its missing part.  Best against 256 x 256, K = 4096: T = 512,
+  // N = 6144 37.9 us (128 x 128) and 94.6; T = 1024, N = 1024 21.5 (64 x 64) and 91.0;
+  // T = 4096, N = 6144 256 x 256 itself, 207 against 245 for 128 x 256.
+  const struct { int pm, pn, cost, least; } shapes[] = {
+      {256, 256, 100, 100}, {128, 256, 60, 60}, {128, 128, 38, 38}, {64, 128, 24, 24}, {64, 64, 15, 20}};
+  int best = 0;
+  double best_cost = 0;
+  for (int i = 0; i < 5; ++i) {
+    const double tiles = ((T + shapes[i].pm - 1) / shapes[i].pm + 1.0) * ((N + shapes[i].pn - 1) / shapes[i].pn);
+    const double rounds = std::max(1.0, tiles / 256);
+    const double cost = std::max<double>(shapes[i].least, 0.5 * (rounds + std::ceil(rounds)) * shapes[i].cost);
+    if (i == 0 || cost < best_cost) best = i, best_cost = cost;
+  }
+  switch (best) {
+    case 0: TILES(256, 256, 2); break;
+    case 1: TILES(128, 256, 3); break;
+    case 2: TILES(128, 128, 4); break;
+    case 3: TILES(64, 128, 3); break;
+    default: TILES(64, 64, 4); break;
+  }
+#undef TILES
   return hipGetLastError();
 }
 

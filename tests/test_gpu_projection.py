@@ -154,3 +154,15 @@ def test_projection_pending_status_writes_nothing(T, N):
     assert sonic.role_projection(role, x, w, w, y, ws, status) == sonic.OK
     torch.cuda.synchronize()
     assert bool((y == 7.0).all()) and int(status.item()) == sonic.ERR_BAD_LAYOUT
+
+
+@pytest.mark.parametrize("T,K,N", [(2050, 64, 6144), (2048, 192, 5900), (900, 64, 6144), (1024, 128, 6001), (512, 320, 6144),
+                                   (300, 64, 6144), (257, 256, 5121), (129, 64, 4097), (1000, 64, 1030), (700, 640, 65),
+                                   (8192, 128, 70), (8193, 64, 257), (20000, 64, 300)])
+def test_projection_tile_shapes(T, K, N):
+    """Every tile shape with a partial last tile in both directions, fewer K steps than its
+    ring holds, and row counts on either side of the switch to the routing kernels."""
+    rng = np.random.default_rng(5 * T + K + N)
+    x, wt, wn = _bits(rng, (T, K)), _bits(rng, (N, K), 0.05), _bits(rng, (N, K), 0.05)
+    for role in (np.where(np.arange(T) % 7 < 2, OL.NEXUS, OL.CURRENT).astype(np.uint8), np.full(T, OL.NEXUS, np.uint8)):
+        check(run(role, x, wt, wn), role, x, wt, wn, f"T={T} K={K} N={N}")

@@ -309,9 +309,11 @@ size_t sonic_decode_workspace_bytes(int32_t batch, int32_t num_q_heads, int32_t 
  * generated token belongs to the current turn, so it sees every retained row.
  * cache_len[b] is incremented on the device, so a decode loop needs no host
  * round trip.  One kernel: the context of each (request, kv-head) is split over
- * up to min(16, 256 / (B * Hkv)) workgroups (three for 256 or more pairs with
- * contexts of 2048 rows and more), and the split that finishes last merges the
- * partials by log-sum-exp.
+ * up to min(16, 256 / (B * Hkv)) workgroups, and the split that finishes last
+ * merges the partials by log-sum-exp.  For 256 or more pairs with max_ctx of 2048
+ * and more, up to 64 requests share about 1024 workgroups in proportion to their
+ * lengths (at most 16 each); more requests, or a workspace without room for those
+ * partials, take three workgroups per pair.
  *
  * With row_role == NULL the cache is a compact one and every row is visible.
  * With row_role != NULL (device uint8 [rows], indexed like cache rows) the

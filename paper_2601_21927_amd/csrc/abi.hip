@@ -1,6 +1,7 @@
 // C ABI entry points: argument checks, workspace carving and kernel launches.
 #include <algorithm>
 #include <cmath>
+#include <cstdint>
 #include <cstdlib>
 #include <cstring>
 #include <mutex>
@@ -43,10 +44,11 @@ hipError_t launch_compact(int batch, int total_tokens, int max_seqlen, int Hkv, 
                           const int32_t *row_cap, int32_t *cache_len, int32_t *keep_idx, int32_t *status,
                           hipStream_t stream);
 int decode_splits(int batch, int Hkv, int max_ctx);
-size_t decode_ws_layout(int batch, int Hkv, int G, int D, int nsplit, DecodeWs *ws, char *base);
-size_t decode_scratch_layout(int batch, int Hkv, int G, int D, int nsplit, DecodeWs *ws, char *base);
+DecodeShape decode_shape(int batch, int Hkv, int G, int D, int max_ctx, bool masked, size_t part_bytes);
+size_t decode_ws_layout(int batch, int Hkv, size_t part_bytes, DecodeWs *ws, char *base);
+size_t decode_scratch_layout(int batch, int Hkv, size_t part_bytes, DecodeWs *ws, char *base);
 hipError_t decode_scratch(hipStream_t stream, char **base);
-hipError_t launch_decode(int batch, int Hq, int Hkv, int D, int max_ctx, int nsplit, uint16_t *kc,
+hipError_t launch_decode(int batch, int Hq, int Hkv, int D, int max_ctx, const DecodeShape &sh, uint16_t *kc,
                          uint16_t *vc, const int64_t *row_off, const int32_t *row_cap, int32_t *cache_len,
                          const uint8_t *row_role, const uint16_t *q, const uint16_t *k_new, const uint16_t *v_new,
                          float scale_log2, float *out, const DecodeWs &ws, int32_t *status, hipStream_t stream);
@@ -554,21 +556,23 @@ int32_t sonic_kv_compact(int32_t batch, int32_t total_tokens, int32_t max_seqlen
 }
 
 // ---------------------------------------------------------------- decode
-static size_t decode_ws_bytes(int32_t batch, int32_t Hq, int32_t d, int32_t nsplit) {
-  // counters: per request, then per (request, kv-head) with Hkv <= Hq
-  const size_t counters = align_up(static_cast<size_t>(batch) * sizeof(int32_t), 256) +
-                          align_up(static_cast<size_t>(batch) * Hq * sizeof(int32_t), 256);
-  const size_t records = nsplit > 1 ? static_cast<size_t>(batch) * Hq * nsplit * (d + 2) * sizeof(float) : 0;
-  return counters + records;
+static size_t decode_counter_bytes(int32_t batch, int32_t Hq) {
+  // per request, then per (request, kv-head) with Hkv <= Hq
+  return align_up(static_cast<size_t>(batch) * sizeof(int32_t), 256) +
+         align_up(static_cast<size_t>(batch) * Hq * sizeof(int32_t), 256);
 }
 
 size_t sonic_decode_workspace_bytes(int32_t batch, int32_t Hq, int32_t d, int32_t max_ctx) {
   if (batch <= 0 || Hq <= 0 || max_ctx <= 0) return 256;
   // enough for any kv-head count the call may use (Hkv dividing Hq, Hq / Hkv <= 8)
-  int nsplit = 1;
-  for (int hkv = 1; hkv <= Hq; ++hkv)
-    if (Hq % hkv == 0 && Hq / hkv <= 8) nsplit = std::max(nsplit, decode_splits(batch, hkv, max_ctx));
-  return align_up(decode_ws_bytes(batch, Hq, d, nsplit), 256);
+  size_t part = 0;
+  for (int hkv = 1; hkv <= Hq; ++hkv) {
+    if (Hq % hkv != 0 || Hq / hkv > 8) continue;
+    const int nsplit = decode_splits(batch, hkv, max_ctx);
+    if (nsplit > 1) part = std::max(part, static_cast<size_t>(batch) * Hq * nsplit * (d + 2) * sizeof(float));
+    part = std::max(part, decode_shape(batch, hkv, Hq / hkv, d, max_ctx, false, SIZE_MAX).part_bytes);
+  }
+  return align_up(decode_counter_bytes(batch, Hq) + part, 256);
 }
 
 // Argument checks shared by the two decode entry points.  Returns SONIC_OK with *empty set
@@ -608,11 +612,13 @@ int32_t sonic_compressed_decode(int32_t batch, int32_t Hq, int32_t Hkv, int32_t 
                                   cache_len, q, k_new, v_new, &softmax_scale, out, dev_status, &empty);
   if (st != SONIC_OK || empty) return st;
   if (!workspace || !aligned(workspace, 256)) return SONIC_ERR_INVALID_ARG;
-  const int nsplit = decode_splits(batch, Hkv, max_ctx);
-  if (workspace_bytes < decode_ws_bytes(batch, Hq, d, nsplit)) return SONIC_ERR_WORKSPACE;
+  const size_t counters = decode_counter_bytes(batch, Hq);
+  const size_t room = workspace_bytes < counters ? 0 : workspace_bytes - counters;
+  const DecodeShape sh = decode_shape(batch, Hkv, Hq / Hkv, d, max_ctx, row_role != nullptr, room);
+  if (workspace_bytes < counters || room < sh.part_bytes) return SONIC_ERR_WORKSPACE;
   DecodeWs ws;
-  decode_ws_layout(batch, Hkv, Hq / Hkv, d, nsplit, &ws, static_cast<char *>(workspace));
-  hipError_t e = launch_decode(batch, Hq, Hkv, d, max_ctx, nsplit, static_cast<uint16_t *>(k_cache),
+  decode_ws_layout(batch, Hkv, sh.part_bytes, &ws, static_cast<char *>(workspace));
+  hipError_t e = launch_decode(batch, Hq, Hkv, d, max_ctx, sh, static_cast<uint16_t *>(k_cache),
                                static_cast<uint16_t *>(v_cache), cache_row_off, cache_row_cap, cache_len, row_role,
                                static_cast<const uint16_t *>(q), static_cast<const uint16_t *>(k_new),
                                static_cast<const uint16_t *>(v_new), static_cast<float>(softmax_scale * kLog2e), out,
@@ -630,15 +636,16 @@ int32_t sonic_compressed_decode_noalloc(int32_t batch, int32_t Hq, int32_t Hkv, 
   const int32_t st = check_decode(batch, Hq, Hkv, d, max_ctx, k_cache, v_cache, cache_row_off, cache_row_cap,
                                   cache_len, q, k_new, v_new, &softmax_scale, out, dev_status, &empty);
   if (st != SONIC_OK || empty) return st;
-  const int nsplit = decode_splits(batch, Hkv, max_ctx);
-  const size_t need = decode_scratch_layout(batch, Hkv, Hq / Hkv, d, nsplit, nullptr, nullptr);
+  const DecodeShape sh = decode_shape(batch, Hkv, Hq / Hkv, d, max_ctx, row_role != nullptr,
+                                      kScratchBytes - kScratchCounterBytes);
+  const size_t need = decode_scratch_layout(batch, Hkv, sh.part_bytes, nullptr, nullptr);
   if (need == 0 || need > kScratchBytes) return SONIC_ERR_WORKSPACE;
   char *base = nullptr;
   hipError_t e = decode_scratch(stream, &base);
   if (e != hipSuccess) return SONIC_ERR_HIP;
   DecodeWs ws;
-  decode_scratch_layout(batch, Hkv, Hq / Hkv, d, nsplit, &ws, base);
-  e = launch_decode(batch, Hq, Hkv, d, max_ctx, nsplit, static_cast<uint16_t *>(k_cache),
+  decode_scratch_layout(batch, Hkv, sh.part_bytes, &ws, base);
+  e = launch_decode(batch, Hq, Hkv, d, max_ctx, sh, static_cast<uint16_t *>(k_cache),
                     static_cast<uint16_t *>(v_cache), cache_row_off, cache_row_cap, cache_len, row_role,
                     static_cast<const uint16_t *>(q), static_cast<const uint16_t *>(k_new),
                     static_cast<const uint16_t *>(v_new), static_cast<float>(softmax_scale * kLog2e), out, ws,

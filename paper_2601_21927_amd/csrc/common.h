@@ -207,9 +207,17 @@ struct PrefillWs {
 
 // Device workspace of the decode; the counters are zero between calls.
 struct DecodeWs {
-  int32_t *done;      // [B]      kv-heads of request b whose splits have all counted in this call
+  int32_t *done;      // [B]      kv-heads of request b finished in this call (balanced: [0] counts the call's)
   int32_t *arrive;    // [B*Hkv]  splits of a (request, kv-head) finished in this call
-  float *part;        // [B*Hkv][nsplit][G*(D+2)] partial (m[G], l[G], acc[G][D]) per split
+  float *part;        // partials: acc[G][D] of every split, then (max, sum)[G] of every split
+};
+
+// How a decode call is cut into workgroups.
+struct DecodeShape {
+  int splits;         // workgroups per (request, kv-head); balanced: per kv-head
+  int target;         // balanced: workgroups per kv-head that share the rows evenly; otherwise 0
+  int waves;          // waves per workgroup
+  size_t part_bytes;  // partials
 };
 
 // The decode's fixed-layout scratch (the entry point that allocates nothing): counters

@@ -28,17 +28,24 @@
 // without rows included, so the last to count knows that every workgroup of
 // the pair has read cache_len; it counts the pair for its request while it
 // loads the partials, and the last pair of a request advances cache_len.
+//
+// BAL (many pairs, long contexts): the rows of the whole batch are shared evenly
+// among the workgroups instead of each request's among its own.  Every workgroup
+// works the shares out from all lengths, so no length may advance while another
+// workgroup has yet to read it: pairs (and workgroups left without rows) count for
+// the whole call, and the last one advances every length.
 #include "common.h"
+
+#include <type_traits>
 
 namespace sonic {
 
-constexpr int kDecWaves = 8;
-constexpr int kDecThreads = kDecWaves * kWave;
 constexpr int kGroupRows = 16;
-constexpr int kMergeBatch = 16;   // partials loaded per memory round trip of the merge
+constexpr int kMaxSplits = 16;   // of a (request, kv-head): the merge loads all its partials in one round trip
 
 typedef short v4i16 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) v4i16 lds_v4i16_t;
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 
 // The K/V loads of the pipeline go straight to LDS and are written as inline
@@ -52,34 +59,46 @@ __device__ __forceinline__ void dma16(const void *src, const uint16_t *dst) {
       reinterpret_cast<uintptr_t>((const __attribute__((address_space(3))) uint16_t *)dst)));
   asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off" : : "v"(src), "s"(lds) : "memory", "m0");
 }
-// A load that bypasses the (non-coherent) caches, for partials another XCD stored
-// write-through; completion is waited for explicitly.
-__device__ __forceinline__ float load_sys(const float *p) {
-  float v;
-  asm volatile("global_load_dword %0, %1, off sc0 sc1" : "=v"(v) : "v"(p) : "memory");
-  return v;
-}
-// atomic add of 1 returning the old value; the result register is written when the
-// atomic returns, so it is read only after an explicit wait_vm<0>
-__device__ __forceinline__ int atomic_inc_pending(int32_t *p) {
-  int old;
-  asm volatile("global_atomic_add %0, %1, %2, off sc0" : "=v"(old) : "v"(p), "v"(1) : "memory");
-  return old;
+// Accesses that bypass the (non-coherent) caches, for partials handed from one XCD to
+// another: buffer operations with the system-scope bits (sc0, sc1), 16 bytes a lane.  Each
+// instruction is a request of its own to memory, so their number counts: the merge of 16
+// splits of 7 heads took 1.2 us longer with 8 bytes a lane, 2.9 with 4.
+constexpr int kSystemScope = 1 | 16;
+typedef __amdgpu_buffer_rsrc_t rsrc_t;
+__device__ __forceinline__ rsrc_t partial_rsrc(float *p) {   // p wave-uniform
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(uniform_ptr(reinterpret_cast<const char *>(p))), 0, -1, 0x00027000);
 }
 
-template <int D, int G, bool MASKED>
-__global__ __launch_bounds__(kDecThreads, 1) void decode_kernel(
+// The value of the lane N places on in the row of 16 lanes (cyclic).
+template <int N> __device__ __forceinline__ float row_rotate(float x) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x120 | N, 0xF, 0xF, false));
+}
+
+// Inclusive sum over the lanes of a wave, without LDS round trips: four shifts inside the
+// rows of 16 lanes, then the rows' totals broadcast to the rows behind.
+__device__ __forceinline__ int wave_scan(int x) {
+  x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xF, 0xF, false);   // row_shr:1
+  x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xF, 0xF, false);   // row_shr:2
+  x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xF, 0xF, false);   // row_shr:4
+  x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xF, 0xF, false);   // row_shr:8
+  x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xA, 0xF, false);   // row_bcast:15 into rows 1 and 3
+  x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xC, 0xF, false);   // row_bcast:31 into rows 2 and 3
+  return x;
+}
+
+template <int D, int G, bool MASKED, int NW, bool BAL>
+__global__ __launch_bounds__(NW * kWave, 2) void decode_kernel(
     uint16_t *__restrict__ kc, uint16_t *__restrict__ vc, const int64_t *__restrict__ row_off,
     const int32_t *__restrict__ row_cap, int32_t *__restrict__ cache_len, const uint8_t *__restrict__ row_role,
     const uint16_t *__restrict__ q, const uint16_t *__restrict__ k_new, const uint16_t *__restrict__ v_new,
-    float *__restrict__ out, DecodeWs ws, int32_t *status, int Hkv, int nsplit_max, int max_ctx,
-    float scale_log2) {
+    float *__restrict__ out, DecodeWs ws, int32_t *status, int Hkv, int nsplit_max, int max_ctx, int batch,
+    int target, float scale_log2) {
   constexpr int KS = D / 32;                   // k steps of the 16x16x32 score product
   constexpr int DB = D / 16;                   // 16-wide d blocks of the value product
   constexpr int DC = D / 8;                    // 16-byte chunks per row
   constexpr int NI = kGroupRows * DC / kWave;  // direct-to-LDS instructions per tensor and group
   constexpr int NG = 2 * NI;                   // loads per lane per group
-  constexpr int REC = G * (D + 2);             // floats of one partial record
+  constexpr int DP = D + 16;                   // row stride of the merge in LDS: heads 16 banks apart
   constexpr int SLOT = kGroupRows * D;         // elements of one tensor's slot
   constexpr int KSWZ = DC - 1;                 // K: 16-byte chunk p of row r at p ^ (r & KSWZ)
   constexpr int VSWZ = DC / 2 - 1;             // V: 32-byte segment s of row r at s ^ (r & VSWZ)
@@ -87,110 +106,189 @@ __global__ __launch_bounds__(kDecThreads, 1) void decode_kernel(
   // ring: [wave][slot 0/1][K, V][16 rows][D] with the swizzles above (K for the
   // row-fragment reads of the scores, V for the transposing reads); reused for the
   // merge of the waves at the end
-  __shared__ __align__(16) uint16_t ring[kDecWaves * 2 * 2 * SLOT];
+  __shared__ __align__(16) uint16_t ring[NW * 2 * 2 * SLOT];
   // each wave's copy of the G query rows (direct-to-LDS, so that no load the
   // compiler counts precedes the pipeline's)
   constexpr int NQ = (G * D * 2 + 1023) / 1024;   // direct-to-LDS instructions for Q
-  __shared__ __align__(16) uint16_t q_lds[kDecWaves][NQ * 512];
+  __shared__ __align__(16) uint16_t q_lds[NW][NQ * 512];
   // split 0: the new token's k and v rows, fetched at the start and appended at the end
   __shared__ __align__(16) uint16_t app_lds[kWave * 8];
   static_assert(2 * DC <= kWave, "one direct-to-LDS instruction holds the new k and v rows");
-  __shared__ float m_lds[kDecWaves][16];
-  __shared__ float l_lds[kDecWaves][16];
+  __shared__ float m_lds[NW][16];
+  __shared__ float l_lds[NW][16];
   __shared__ int s_last;
-  static_assert(sizeof(float) * kDecWaves * G * D <= sizeof(uint16_t) * kDecWaves * 4 * SLOT,
+  static_assert(sizeof(float) * NW * G * DP <= sizeof(uint16_t) * NW * 4 * SLOT,
                 "the merge fits in the ring");
 
-  const int split = blockIdx.x;
   const int kvh = blockIdx.y;
-  const int b = blockIdx.z;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const int lane = threadIdx.x % kWave;
   const int Hq = Hkv * G;
-  // the status word, the length and the request's first cache row are requested
-  // together (one round trip for all three)
-  const int32_t pending = __hip_atomic_load(status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  const int len = cache_len[b];
-  const int cap = row_cap[b];
-  const int64_t base = row_off[b];
-  asm volatile("" ::"s"(base));
-  // A pending error other than a capacity error (a layout error of an earlier call)
-  // stops the whole call: nothing is appended, written or advanced.  Only capacity
-  // errors can appear during the call (raised below, per request), so every
-  // workgroup of the call takes the same decision and no counter is touched.
-  if (pending != 0 && pending != SONIC_ERR_CAPACITY) return;
-  const int n_ctx = len + 1;
-  if (n_ctx > cap || n_ctx > max_ctx) {   // uniform over the request: no append, no output
-    if (split == 0 && kvh == 0 && threadIdx.x == 0) raise_status(status, SONIC_ERR_CAPACITY);
-    return;
+  const int nsplit = gridDim.x;   // BAL: workgroups of a kv-head
+  int split, b, nsp, R, len;
+  int64_t base;
+  // BAL: the workgroup's plan.  Lane l looks at request l (at most 64): its length,
+  // capacity and first row, all requested together with the status word.  A split is R
+  // rows, the same for every request: the batch's rows over the kv-head's `target`
+  // workgroups, no fewer than 256 rows and no less than a sixteenth of the longest
+  // request.  Request l then takes ceil(rows / R) consecutive workgroups (target + batch
+  // are launched, the ones left over have nothing to do).
+  int first = 0, lane_ctx = 0, used = 0;
+  if constexpr (BAL) {
+    const int l = threadIdx.x % kWave, lb = min(l, batch - 1);
+    const int32_t pending = __hip_atomic_load(status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const int ll = cache_len[lb], lc = row_cap[lb];
+    const int64_t lo = row_off[lb];
+    if (pending != 0 && pending != SONIC_ERR_CAPACITY) return;
+    const bool fits = ll + 1 <= lc && ll + 1 <= max_ctx;
+    if (__any(!fits) && blockIdx.x == 0 && kvh == 0 && threadIdx.x == 0) raise_status(status, SONIC_ERR_CAPACITY);
+    lane_ctx = l < batch && fits ? ll + 1 : 0;
+    const int groups = (lane_ctx + kGroupRows - 1) / kGroupRows;
+    const int total = __builtin_amdgcn_readlane(wave_scan(groups), kWave - 1);
+    int longest = groups;
+#pragma unroll
+    for (int o = 8; o > 0; o >>= 1) longest = max(longest, __shfl_xor(longest, o));
+    longest = max(max(__builtin_amdgcn_readlane(longest, 0), __builtin_amdgcn_readlane(longest, 16)),
+                  max(__builtin_amdgcn_readlane(longest, 32), __builtin_amdgcn_readlane(longest, 48)));
+    const int rg = max(max(256 / kGroupRows, (longest + kMaxSplits - 1) / kMaxSplits), (total + target - 1) / target);
+    const int mine = (groups + rg - 1) / rg;
+    const int upto = wave_scan(mine);
+    used = __builtin_amdgcn_readlane(upto, kWave - 1);
+    const int w = blockIdx.x;
+    b = __popcll(__ballot(upto <= w));
+    R = rg * kGroupRows;
+    if (w < used) {
+      nsp = __builtin_amdgcn_readlane(mine, b);
+      first = __builtin_amdgcn_readlane(upto, b) - nsp;
+      len = __builtin_amdgcn_readlane(ll, b);
+      const uint32_t lo32 = __builtin_amdgcn_readlane(static_cast<int>(lo), b);
+      const uint32_t hi32 = __builtin_amdgcn_readlane(static_cast<int>(lo >> 32), b);
+      base = static_cast<int64_t>((static_cast<uint64_t>(hi32) << 32) | lo32);
+    } else {
+      b = 0, nsp = 0, first = w, len = 0, base = 0;
+    }
+    split = w - first;
+  } else {
+    split = blockIdx.x;
+    b = blockIdx.z;
+    // the status word, the length and the request's first cache row are requested
+    // together (one round trip for all three)
+    const int32_t pending = __hip_atomic_load(status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    len = cache_len[b];
+    const int cap = row_cap[b];
+    base = row_off[b];
+    asm volatile("" ::"s"(base));
+    // A pending error other than a capacity error (a layout error of an earlier call)
+    // stops the whole call: nothing is appended, written or advanced.  Only capacity
+    // errors can appear during the call (raised below, per request), so every
+    // workgroup of the call takes the same decision and no counter is touched.
+    if (pending != 0 && pending != SONIC_ERR_CAPACITY) return;
+    if (len + 1 > cap || len + 1 > max_ctx) {   // uniform over the request: no append, no output
+      if (split == 0 && kvh == 0 && threadIdx.x == 0) raise_status(status, SONIC_ERR_CAPACITY);
+      return;
+    }
+    // split ranges: R rows each, a multiple of the group size
+    R = ((len + nsplit_max) / nsplit_max + kGroupRows - 1) / kGroupRows * kGroupRows;
+    nsp = (len + R) / R;   // splits that hold rows; the others have nothing to do
   }
-  // split ranges: R rows each, a multiple of the group size
-  const int R = ((n_ctx + nsplit_max - 1) / nsplit_max + kGroupRows - 1) / kGroupRows * kGroupRows;
-  const int nsp = (n_ctx + R - 1) / R;   // splits that hold rows; the others have nothing to do
-  const int nsplit = gridDim.x;
+  const int n_ctx = len + 1;
   const int pair = b * Hkv + kvh;
   float *orow = out + (static_cast<size_t>(b) * Hq + kvh * G) * D;
+  // the pair's partials: [split][G][D] values, then, behind every pair's, [split][G] (max, sum)
+  const size_t slot0 = BAL ? static_cast<size_t>(kvh) * nsplit + first : static_cast<size_t>(pair) * nsplit_max;
+  float *const acc_rec = ws.part + slot0 * (G * D);
+  float *const stat_rec = ws.part + static_cast<size_t>(gridDim.x) * gridDim.y * gridDim.z * (G * D) + slot0 * (2 * G);
+  // BAL: a pair's last workgroup, and every workgroup without rows, counts once in done[0];
+  // the last of the call advances every length.  A workgroup has read the lengths before
+  // it counts, so none can still see an advanced one.
+  const int all = BAL ? Hkv * (__popcll(__ballot(lane_ctx > 0)) + nsplit - used) : Hkv;
+  auto count = [&]() {
+    return __hip_atomic_fetch_add(&ws.done[BAL ? 0 : b], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  };
+  auto advance = [&](int old) {   // the first wave; `old` is its first lane's
+    if (__builtin_amdgcn_readfirstlane(old) != all - 1) return;
+    if (BAL) {
+      if (lane_ctx > 0) cache_len[threadIdx.x] = lane_ctx;
+    } else if (threadIdx.x == 0) {
+      cache_len[b] = n_ctx;
+    }
+    if (threadIdx.x == 0) ws.done[BAL ? 0 : b] = 0;
+  };
 
   // Every split counts itself once, after its partial (if any) is stored.  The last
-  // to count merges the partials of the nsp splits with rows by log-sum-exp, a batch
-  // of kMergeBatch per memory round trip, writes the output, and counts the pair for its
-  // request while the partials load; the last pair of a request advances the length.
+  // to count merges the partials of the nsp splits with rows by log-sum-exp, all of them
+  // in one memory round trip, writes the output, and counts the pair for its request
+  // while the partials load; the last pair of a request advances the length.
   auto finish_pair = [&]() {
-    if (threadIdx.x == 0) s_last = (atomicAdd(&ws.arrive[pair], 1) == nsplit - 1);
+    if (threadIdx.x == 0) s_last = (atomicAdd(&ws.arrive[pair], 1) == (BAL ? nsp : nsplit) - 1);
     __syncthreads();
     if (!s_last) return;
+    // Thread u merges values 4u .. 4u + 3 (of q-head u / (D / 4)).  For the weights, lane
+    // 16 j + i of a wave takes split i of the wave's j-th q-head.
+    static_assert(G * D / 4 <= NW * kWave && kMaxSplits == 16, "one pass; a row of lanes holds a head's splits");
+    if (wave * kWave >= G * D / 4) return;
+    constexpr int LH = D / 4;   // lanes per q-head
+    const int u = min(static_cast<int>(threadIdx.x), G * D / 4 - 1);
+    const rsrc_t ra = partial_rsrc(acc_rec), rs = partial_rsrc(stat_rec);
+    const int head = min(wave * (kWave / LH) + lane / 16, G - 1), sp = lane % 16;
+    const auto ml = __builtin_amdgcn_raw_buffer_load_b64(rs, (min(sp, nsp - 1) * G + head) * 8, 0, kSystemScope);
+    f32x4 a[kMaxSplits];
+    auto load = [&](auto n) {
+#pragma unroll
+      for (int i = 0; i < decltype(n)::value; ++i)
+        a[i] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(ra, u * 16, min(i, nsp - 1) * (G * D * 4), kSystemScope));
+    };
+    if (nsp <= 4) load(std::integral_constant<int, 4>{});
+    else load(std::integral_constant<int, kMaxSplits>{});
+    __builtin_amdgcn_sched_barrier(0);
+    // behind the loads, so that the round trips pass together (the compiler waits for an
+    // atomic's result on the spot)
     int old_done = 0;
-    if (threadIdx.x == 0) old_done = atomic_inc_pending(&ws.done[b]);
-    const float *recs = ws.part + static_cast<size_t>(pair) * nsplit_max * REC;
-    for (int idx = threadIdx.x; idx < G * D; idx += kDecThreads) {
-      const int hh = idx / D, dd = idx % D;
-      float M = -INFINITY, L = 0.f, A = 0.f;
-      for (int sp0 = 0; sp0 < nsp; sp0 += kMergeBatch) {
-        float m[kMergeBatch], l[kMergeBatch], a[kMergeBatch];
+    if (threadIdx.x == 0) old_done = count();
+    const float m = sp < nsp ? __uint_as_float(ml[0]) : -INFINITY;
+    float top = m;
+    top = fmaxf(top, row_rotate<8>(top));
+    top = fmaxf(top, row_rotate<4>(top));
+    top = fmaxf(top, row_rotate<2>(top));
+    top = fmaxf(top, row_rotate<1>(top));
+    const float w = m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m - top);
+    float sum = w == 0.f ? 0.f : w * __uint_as_float(ml[1]);
+    sum += row_rotate<8>(sum);
+    sum += row_rotate<4>(sum);
+    sum += row_rotate<2>(sum);
+    sum += row_rotate<1>(sum);
+    const int from = lane / LH * 16;
+    f32x4 A = {0.f, 0.f, 0.f, 0.f};
+    auto fold = [&](auto n) {
 #pragma unroll
-        for (int u = 0; u < kMergeBatch; ++u) {
-          const float *r = recs + static_cast<size_t>(min(sp0 + u, nsp - 1)) * REC + hh * (D + 2);
-          m[u] = load_sys(r);
-          l[u] = load_sys(r + 1);
-          a[u] = load_sys(r + 2 + dd);
-        }
-        wait_vm<0>();
+      for (int i = 0; i < decltype(n)::value; ++i) {
+        const float wi = __shfl(w, from + i);   // 0 past the splits
 #pragma unroll
-        for (int u = 0; u < kMergeBatch; ++u) asm volatile("" : "+v"(m[u]), "+v"(l[u]), "+v"(a[u]));
-        float Mb = M;
-#pragma unroll
-        for (int u = 0; u < kMergeBatch; ++u)
-          if (sp0 + u < nsp) Mb = fmaxf(Mb, m[u]);
-        const float c = (M == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(M - Mb);
-        L *= c;
-        A *= c;
-#pragma unroll
-        for (int u = 0; u < kMergeBatch; ++u) {
-          const float w = (sp0 + u < nsp && m[u] != -INFINITY) ? __builtin_amdgcn_exp2f(m[u] - Mb) : 0.f;
-          L = fmaf(w, l[u], L);
-          A = fmaf(w, a[u], A);
-        }
-        M = Mb;
+        for (int e = 0; e < 4; ++e) A[e] = fmaf(wi, a[i][e], A[e]);
       }
-      orow[idx] = A / L;
-    }
-    wait_vm<0>();
-    if (threadIdx.x == 0) {
-      asm volatile("" : "+v"(old_done));
-      ws.arrive[pair] = 0;
-      if (old_done == Hkv - 1) {
-        cache_len[b] = n_ctx;
-        ws.done[b] = 0;
-      }
-    }
+    };
+    if (nsp <= 4) fold(std::integral_constant<int, 4>{});
+    else fold(std::integral_constant<int, kMaxSplits>{});
+    const float L = __shfl(sum, from);
+    if (threadIdx.x < G * D / 4) *reinterpret_cast<f32x4 *>(orow + 4 * u) = f32x4{A[0] / L, A[1] / L, A[2] / L, A[3] / L};
+    if (threadIdx.x == 0) ws.arrive[pair] = 0;
+    if (threadIdx.x < kWave) advance(old_done);
   };
   if (split >= nsp) {   // no rows (only when nsplit > 1)
-    finish_pair();
+    __syncthreads();    // every wave has read the lengths: the workgroup may count
+    if (!BAL) {
+      finish_pair();
+    } else if (threadIdx.x < kWave) {
+      int old = 0;
+      if (threadIdx.x == 0) old = count();
+      advance(old);
+    }
     return;
   }
+  const bool whole = BAL ? nsp == 1 : nsplit == 1;   // the split is all of the pair's context
   const int r_begin = split * R;
   const int r_end = min(n_ctx, r_begin + R);
   const int ngroups = (r_end - r_begin + kGroupRows - 1) / kGroupRows;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-  const int lane = threadIdx.x % kWave;
   const int col = lane & 15;       // score column (q-head) / value-product column
   const int quarter = lane >> 4;   // score rows 4*quarter .. +3
   const size_t row_stride = static_cast<size_t>(Hkv) * D;
@@ -313,14 +411,23 @@ __global__ __launch_bounds__(kDecThreads, 1) void decode_kernel(
     f32x4 p;
 #pragma unroll
     for (int i = 0; i < 4; ++i) p[i] = (x[i] == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(x[i] - m_run);
+    // Each probability goes into the product as the sum of two bf16 values, its rounding and
+    // the rounding of what that left (2^-17 of it at most): a single one left the output
+    // 1.2e-3 to 1.6e-3 from 64 bits, more the fewer ranges a context is cut into (the top key
+    // of a range rounds to exactly 1).  The sum is taken over the same rounded values, so
+    // the output stays a convex combination of the V rows (see the prefill).  Both values
+    // of a lane's four rows share one product of depth 32, whose V operand holds the rows
+    // twice: as fast as the one of depth 16 with the single values.
     const bf16x4 pr = __builtin_convertvector(p, bf16x4);
-    const v4i16 pb = __builtin_bit_cast(v4i16, pr);
-    // the sum is taken over the rounded probabilities the value product uses, so the
-    // output stays a convex combination of the V rows (see the prefill)
+    const f32x4 left = p - __builtin_convertvector(pr, f32x4);
+    const bf16x4 pl = __builtin_convertvector(left, bf16x4);
+    const bf16x8 pp = __builtin_shufflevector(pr, pl, 0, 1, 2, 3, 4, 5, 6, 7);
     {
       const bf16x2 ones = __builtin_bit_cast(bf16x2, 0x3F803F80u);
       l_run = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(pr, pr, 0, 1), ones, l_run, false);
       l_run = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(pr, pr, 2, 3), ones, l_run, false);
+      l_run = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(pl, pl, 0, 1), ones, l_run, false);
+      l_run = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(pl, pl, 2, 3), ones, l_run, false);
     }
     const uint16_t *vslot = kslot + SLOT;
 #pragma unroll
@@ -328,25 +435,26 @@ __global__ __launch_bounds__(kDecThreads, 1) void decode_kernel(
       const uint16_t *pa = vslot + tr_off + ((db ^ tr_swz) * 16);
       // C-style cast: the transposing read takes an LDS-qualified pointer
       const v4i16 a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16_t *)pa);
-      oacc[db] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, pb, oacc[db], 0, 0, 0);
+      const bf16x8 aa = __builtin_bit_cast(bf16x8, __builtin_shufflevector(a, a, 0, 1, 2, 3, 0, 1, 2, 3));
+      oacc[db] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(aa, pp, oacc[db], 0, 0, 0);
     }
     __builtin_amdgcn_s_waitcnt(15 | (3 << 14) | (7 << 4));   // lgkmcnt(0): slot s may be refilled
   };
 
   // two-deep pipeline: a slot is refilled as soon as its group has been processed
-  int ga = wave, gb = wave + kDecWaves;   // the groups in ring slots 0 and 1
+  int ga = wave, gb = wave + NW;   // the groups in ring slots 0 and 1
   issue(ga, 0);
   issue(gb, 1);
   wait_vm<NG>();                          // Q and slot 0 have landed (slot 1 may not have)
   read_q();
   while (ga < ngroups) {
     process(ga, 0);
-    ga += 2 * kDecWaves;
+    ga += 2 * NW;
     issue(ga, 0);
     wait_vm<NG>();                        // slot 1 has landed (slot 0 may not have)
     if (gb >= ngroups) break;
     process(gb, 1);
-    gb += 2 * kDecWaves;
+    gb += 2 * NW;
     issue(gb, 1);
     wait_vm<NG>();
   }
@@ -363,45 +471,50 @@ __global__ __launch_bounds__(kDecThreads, 1) void decode_kernel(
     l_lds[wave][col] = l_run;
   }
   __syncthreads();   // every wave is done with the ring
-  float *acc_lds = reinterpret_cast<float *>(ring);   // [wave][G][D]
+  // [wave][G][DP]: a lane's four values are consecutive d, written at once; with rows of D
+  // floats the G heads of a column block all met in one bank
+  float *acc_lds = reinterpret_cast<float *>(ring);
   if (col < G) {
 #pragma unroll
     for (int db = 0; db < DB; ++db)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) acc_lds[(wave * G + col) * D + 16 * db + 4 * quarter + i] = oacc[db][i];
+      *reinterpret_cast<f32x4 *>(&acc_lds[(wave * G + col) * DP + 16 * db + 4 * quarter]) = oacc[db];
   }
   __syncthreads();
 
-  float *rec = ws.part + (static_cast<size_t>(pair) * nsplit_max + split) * REC;
-  for (int idx = threadIdx.x; idx < G * D; idx += kDecThreads) {
-    const int hh = idx / D, dd = idx % D;
+  for (int u = threadIdx.x; u < G * D / 4; u += NW * kWave) {
+    const int hh = u / (D / 4), dd = 4 * (u % (D / 4));
     float M = -INFINITY;
 #pragma unroll
-    for (int w = 0; w < kDecWaves; ++w) M = fmaxf(M, m_lds[w][hh]);
-    float L = 0.f, A = 0.f;
+    for (int w = 0; w < NW; ++w) M = fmaxf(M, m_lds[w][hh]);
+    float L = 0.f;
+    f32x4 A = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int w = 0; w < kDecWaves; ++w) {
+    for (int w = 0; w < NW; ++w) {
       const float sc = (m_lds[w][hh] == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(m_lds[w][hh] - M);
       L = fmaf(sc, l_lds[w][hh], L);
-      A = fmaf(sc, acc_lds[(w * G + hh) * D + dd], A);
+      const f32x4 a = *reinterpret_cast<const f32x4 *>(&acc_lds[(w * G + hh) * DP + dd]);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) A[e] = fmaf(sc, a[e], A[e]);
     }
-    if (nsplit == 1) {
-      orow[idx] = A / L;
+    if (whole) {
+      *reinterpret_cast<f32x4 *>(orow + 4 * u) = f32x4{A[0] / L, A[1] / L, A[2] / L, A[3] / L};
     } else {   // write-through at system scope (see the top of the file)
+      __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, A), partial_rsrc(acc_rec), u * 16, split * (G * D * 4),
+                                             kSystemScope);
       if (dd == 0) {
-        __hip_atomic_store(rec + hh * (D + 2), M, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-        __hip_atomic_store(rec + hh * (D + 2) + 1, L, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        const u32x2 ml = {__float_as_uint(M), __float_as_uint(L)};
+        __builtin_amdgcn_raw_buffer_store_b64(ml, partial_rsrc(stat_rec), (split * G + hh) * 8, 0, kSystemScope);
       }
-      __hip_atomic_store(rec + hh * (D + 2) + 2 + dd, A, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     }
   }
-  if (nsplit > 1) {
+  if (!whole) {
     wait_vm<0>();      // this thread's partial is stored
     __syncthreads();   // ... and every thread's
     finish_pair();
-  } else if (threadIdx.x == 0 && atomicAdd(&ws.done[b], 1) == Hkv - 1) {
-    cache_len[b] = n_ctx;
-    ws.done[b] = 0;
+  } else if (threadIdx.x < kWave) {
+    int old = 0;
+    if (threadIdx.x == 0) old = count();
+    advance(old);
   }
 }
 
@@ -421,61 +534,98 @@ int decode_splits(int batch, int Hkv, int max_ctx) {
   long s = 256 / pairs;
   const long by_rows = (static_cast<long>(max_ctx) + 255) / 256;
   if (s > by_rows) s = by_rows;
-  if (s > kMergeBatch) s = kMergeBatch;
+  if (s > kMaxSplits) s = kMaxSplits;
   return static_cast<int>(s < 1 ? 1 : s);
+}
+
+// How a call is cut into workgroups.
+DecodeShape decode_shape(int batch, int Hkv, int G, int D, int max_ctx, bool masked, size_t part_bytes) {
+  DecodeShape sh{decode_splits(batch, Hkv, max_ctx), 0, 8, 0};
+  const long pairs = static_cast<long>(batch) * Hkv;
+  auto part = [&](long slots) { return static_cast<size_t>(slots) * G * (D + 2) * sizeof(float); };
+  // Evenly shared rows (see the kernel) where a call fills the GPU several times over and
+  // contexts may be long and uneven.  512 four-wave workgroups are resident; a request's
+  // last split is half empty on average, so `target` aims at whole rounds of 512 with
+  // half a split per pair to spare: 64 contexts of 180 .. 4300 rows, 8 kv-heads, 83.8 us
+  // with three splits per pair, 80.0 so (two rounds aimed at; 90 with one); 32 contexts of
+  // 375 .. 8192 rows 90.9 and 80.7.  Fewer pairs keep a split per pair and range: there
+  // the plan and the count over the whole call cost 2.4 us of 12 and evenness gains less.
+  if (!masked && batch <= kWave && pairs >= 256 && max_ctx >= 2048) {
+    long rounds = 2;
+    while (512 * rounds - pairs / 2 < pairs) ++rounds;
+    const long target = (512 * rounds - pairs / 2 + Hkv - 1) / Hkv;
+    if (part((target + batch) * Hkv) <= part_bytes) {
+      sh.target = static_cast<int>(target);
+      sh.splits = static_cast<int>(target + batch);
+    }
+  }
+  const long slots = sh.target > 0 ? static_cast<long>(sh.splits) * Hkv : pairs * sh.splits;
+  sh.part_bytes = sh.splits > 1 ? part(slots) : 0;
+  // Four waves, two workgroups per CU, where there are enough workgroups: one starts and
+  // merges while the other streams (512 pairs of 200 rows 13.7 us with four, 18.1 with
+  // eight), and with one workgroup per CU and short ranges, where starting and merging
+  // are most of the call (64 pairs of 1.3k rows in four ranges each 12.1 and 13.0).  With
+  // fewer workgroups, or long ranges on one per CU, eight keep more loads in flight
+  // (8 pairs of 8k rows 11.8, with four 13.0; 400 pairs of 80 .. 1900 rows 28.0 and
+  // 33.0), as where the second round of 512 would be at most half full (768 workgroups of
+  // 1.5k rows: 118.6, with four 121.8).  D = 64 fits twice with eight (64 pairs of 4k rows
+  // 13.0, with four 13.4).
+  const bool two = (slots >= 480 && slots <= 512) || slots > 768;
+  const bool brief = slots >= 256 && slots < 480 && max_ctx <= 512L * sh.splits;
+  if (sh.target > 0 || (!masked && D == 128 && (two || brief))) sh.waves = 4;
+  return sh;
 }
 
 // Fixed layout of a scratch array shared by calls of different shapes: the counters
 // sit at the same offsets for every call (each call leaves them at zero), the partial
 // records after them.  Returns the bytes a call needs, or 0 when its requests or
 // (request, kv-head) pairs exceed the fixed counter regions.
-size_t decode_scratch_layout(int batch, int Hkv, int G, int D, int nsplit, DecodeWs *ws, char *base) {
+size_t decode_scratch_layout(int batch, int Hkv, size_t part_bytes, DecodeWs *ws, char *base) {
   if (batch > kScratchMaxRequests || static_cast<long>(batch) * Hkv > kScratchMaxPairs) return 0;
-  const size_t pbytes = nsplit > 1 ? static_cast<size_t>(batch) * Hkv * nsplit * G * (D + 2) * sizeof(float) : 0;
   if (ws) {
     ws->done = reinterpret_cast<int32_t *>(base);
     ws->arrive = reinterpret_cast<int32_t *>(base + kScratchMaxRequests * sizeof(int32_t));
     ws->part = reinterpret_cast<float *>(base + kScratchCounterBytes);
   }
-  return kScratchCounterBytes + pbytes;
+  return kScratchCounterBytes + part_bytes;
 }
 
-size_t decode_ws_layout(int batch, int Hkv, int G, int D, int nsplit, DecodeWs *ws, char *base) {
+size_t decode_ws_layout(int batch, int Hkv, size_t part_bytes, DecodeWs *ws, char *base) {
   const size_t dbytes = (static_cast<size_t>(batch) * sizeof(int32_t) + 255) / 256 * 256;
   const size_t abytes = (static_cast<size_t>(batch) * Hkv * sizeof(int32_t) + 255) / 256 * 256;
-  const size_t pbytes = nsplit > 1 ? static_cast<size_t>(batch) * Hkv * nsplit * G * (D + 2) * sizeof(float) : 0;
   if (ws) {
     ws->done = reinterpret_cast<int32_t *>(base);
     ws->arrive = reinterpret_cast<int32_t *>(base + dbytes);
     ws->part = reinterpret_cast<float *>(base + dbytes + abytes);
   }
-  return dbytes + abytes + pbytes;
+  return dbytes + abytes + part_bytes;
 }
 
 template <int D, int G>
-static void launch_decode_dg(dim3 grid, int batch, int Hkv, int max_ctx, int nsplit, uint16_t *kc, uint16_t *vc,
+static void launch_decode_dg(int batch, int Hkv, int max_ctx, const DecodeShape &sh, uint16_t *kc, uint16_t *vc,
                              const int64_t *row_off, const int32_t *row_cap, int32_t *cache_len,
                              const uint8_t *row_role, const uint16_t *q, const uint16_t *k_new, const uint16_t *v_new,
                              float scale_log2, float *out, DecodeWs ws, int32_t *status, hipStream_t stream) {
-  if (row_role != nullptr)
-    decode_kernel<D, G, true><<<grid, dim3(kDecThreads), 0, stream>>>(kc, vc, row_off, row_cap, cache_len, row_role,
-                                                                      q, k_new, v_new, out, ws, status, Hkv, nsplit,
-                                                                      max_ctx, scale_log2);
-  else
-    decode_kernel<D, G, false><<<grid, dim3(kDecThreads), 0, stream>>>(kc, vc, row_off, row_cap, cache_len,
-                                                                       row_role, q, k_new, v_new, out, ws, status,
-                                                                       Hkv, nsplit, max_ctx, scale_log2);
+  const dim3 grid(sh.splits, Hkv, sh.target > 0 ? 1 : batch);
+#define GO(MASKED, NW, BAL)                                                                                  \
+  decode_kernel<D, G, MASKED, NW, BAL><<<grid, dim3(NW * kWave), 0, stream>>>(                               \
+      kc, vc, row_off, row_cap, cache_len, row_role, q, k_new, v_new, out, ws, status, Hkv, sh.splits, max_ctx, \
+      batch, sh.target, scale_log2)
+  if (row_role != nullptr) GO(true, 8, false);
+  else if (sh.target > 0) GO(false, 4, true);
+  else if (sh.waves == 4) GO(false, 4, false);
+  else GO(false, 8, false);
+#undef GO
 }
 
-hipError_t launch_decode(int batch, int Hq, int Hkv, int D, int max_ctx, int nsplit, uint16_t *kc, uint16_t *vc,
-                         const int64_t *row_off, const int32_t *row_cap, int32_t *cache_len, const uint8_t *row_role,
-                         const uint16_t *q, const uint16_t *k_new, const uint16_t *v_new, float scale_log2,
-                         float *out, const DecodeWs &ws, int32_t *status, hipStream_t stream) {
+hipError_t launch_decode(int batch, int Hq, int Hkv, int D, int max_ctx, const DecodeShape &sh, uint16_t *kc,
+                         uint16_t *vc, const int64_t *row_off, const int32_t *row_cap, int32_t *cache_len,
+                         const uint8_t *row_role, const uint16_t *q, const uint16_t *k_new, const uint16_t *v_new,
+                         float scale_log2, float *out, const DecodeWs &ws, int32_t *status, hipStream_t stream) {
   const int G = Hq / Hkv;
-  dim3 grid(nsplit, Hkv, batch);
 #define DEC(DD, GG)                                                                                               \
   case GG:                                                                                                        \
-    launch_decode_dg<DD, GG>(grid, batch, Hkv, max_ctx, nsplit, kc, vc, row_off, row_cap, cache_len, row_role, q, \
+    launch_decode_dg<DD, GG>(batch, Hkv, max_ctx, sh, kc, vc, row_off, row_cap, cache_len, row_role, q, \
                              k_new, v_new, scale_log2, out, ws, status, stream);                                  \
     break;
 #define DEC_ALL_G(DD)                     \

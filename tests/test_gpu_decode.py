@@ -226,3 +226,58 @@ def test_decode_default_scale_is_one_over_sqrt_d():
         torch.cuda.synchronize()
         outs.append(out.cpu().numpy())
     assert np.array_equal(outs[0], outs[1])
+
+
+def plain_caches(rng, lens, room, Hkv, d):
+    """Caches of the given lengths with `room` rows to spare: (cache, k bits, v bits)."""
+    from paper_2601_21927_amd.runner import CompactCache
+    cap = np.asarray(lens, np.int64) + room
+    off = np.concatenate([[0], np.cumsum(cap)[:-1]])
+    cache = CompactCache(int(cap.sum()), Hkv, d, off, cap, "cuda")
+    k, v = (W.f32_to_bf16_bits(rng.standard_normal((int(cap.sum()), Hkv, d)).astype(np.float32)) for _ in range(2))
+    cache.k.copy_(bf16_to_device(k))
+    cache.v.copy_(bf16_to_device(v))
+    cache.length.copy_(torch.from_numpy(np.asarray(lens, np.int32)))
+    return cache, k, v
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,d,lens,max_ctx", [
+    (64, 16, 4, 128, (0, 1, 15, 16, 255, 256, 257, 700), 2048),     # shared evenly, 64 requests
+    (37, 56, 7, 64, (3, 300, 511, 512, 513), 4096),                  # ... odd counts, eight heads a group
+    (32, 8, 8, 128, (2500, 40), 2600),                               # ... a request of many splits, one head a group
+    (64, 28, 4, 128, (5, 60, 200), 256),                             # a split per pair, four waves
+    (12, 8, 8, 128, (100, 700), 1024),                               # fewer workgroups than CUs: eight waves
+    (8, 32, 8, 128, (900, 37), 1000),                                # four splits, four waves
+    (65, 16, 4, 64, (90, 300), 2048)])                               # more requests than a wave has lanes
+def test_decode_work_split(B, Hq, Hkv, d, lens, max_ctx):
+    """Every way a call is cut into workgroups, over uneven lengths with a request at its
+    capacity among them: outputs, appended rows, lengths, two calls in a row."""
+    H.need_gpu()
+    rng = np.random.default_rng(B + Hq + d)
+    lens = np.array([lens[b % len(lens)] for b in range(B)], np.int64)
+    cache, k, v = plain_caches(rng, lens, 2, Hkv, d)
+    full = B // 2                                  # this request has no room left
+    cache.row_cap[full] = int(lens[full])
+    off = cache.row_off_host
+    status = torch.zeros(1, dtype=torch.int32, device="cuda")
+    out = torch.full((B, Hq, d), 7.0, dtype=torch.float32, device="cuda")
+    for t in range(2):
+        q, kn, vn = (W.f32_to_bf16_bits(rng.standard_normal((B, h, d)).astype(np.float32)) for h in (Hq, Hkv, Hkv))
+        assert cache.decode(bf16_to_device(q), bf16_to_device(kn), bf16_to_device(vn), out, status, max_ctx) == sonic.OK
+        torch.cuda.synchronize()
+        assert int(status.item()) == sonic.ERR_CAPACITY
+        got, gk, gv = out.cpu().numpy(), bf16_to_host(cache.k), bf16_to_host(cache.v)
+        for b in range(B):
+            o, n = int(off[b]), int(lens[b])
+            if b == full:
+                assert (got[b] == 7.0).all() and np.array_equal(gk[o:o + n + 2], k[o:o + n + 2])
+                continue
+            if b < 8 or b % 7 == 0 or b == B - 1:
+                want = OD.decode_step(q[b], k[o:o + n], v[o:o + n], kn[b], vn[b])
+                err = np.abs(got[b] - want).max()
+                # probabilities carry 16 bits: 2^-16 of the largest value, and the fp32 sums
+                assert err <= 1e-4, f"request {b} step {t}: {err:.2e}"
+            k[o + n], v[o + n] = kn[b], vn[b]
+            assert np.array_equal(gk[o:o + n + 1], k[o:o + n + 1]) and np.array_equal(gv[o:o + n + 1], v[o:o + n + 1])
+            lens[b] += 1
+        assert np.array_equal(cache.length.cpu().numpy(), lens)

@@ -35,6 +35,7 @@
 // workgroup has yet to read it: pairs (and workgroups left without rows) count for
 // the whole call, and the last one advances every length.
 #include "common.h"
+#include "scan.h"
 
 #include <type_traits>
 
@@ -72,18 +73,6 @@ __device__ __forceinline__ rsrc_t partial_rsrc(float *p) {   // p wave-uniform
 // The value of the lane N places on in the row of 16 lanes (cyclic).
 template <int N> __device__ __forceinline__ float row_rotate(float x) {
   return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x120 | N, 0xF, 0xF, false));
-}
-
-// Inclusive sum over the lanes of a wave, without LDS round trips: four shifts inside the
-// rows of 16 lanes, then the rows' totals broadcast to the rows behind.
-__device__ __forceinline__ int wave_scan(int x) {
-  x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xF, 0xF, false);   // row_shr:1
-  x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xF, 0xF, false);   // row_shr:2
-  x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xF, 0xF, false);   // row_shr:4
-  x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xF, 0xF, false);   // row_shr:8
-  x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xA, 0xF, false);   // row_bcast:15 into rows 1 and 3
-  x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xC, 0xF, false);   // row_bcast:31 into rows 2 and 3
-  return x;
 }
 
 template <int D, int G, bool MASKED, int NW, bool BAL>

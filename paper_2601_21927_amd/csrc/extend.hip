@@ -63,7 +63,7 @@ __global__ __launch_bounds__(kExtendThreads) void plan_extend_kernel(
     int batch, const int32_t *__restrict__ nexus_cu, const int32_t *__restrict__ keep_len,
     const int32_t *__restrict__ body_len, const int32_t *__restrict__ cache_len, const int32_t *__restrict__ row_cap,
     int max_rows, int total_new, PrefillWs ws, int32_t *status) {
-  __shared__ int lds[kExtendThreads / kWave + 1];
+  __shared__ int lds[3 * (kExtendThreads / kWave)];
   __shared__ int s_ok;
   const int b = blockIdx.x;
   if (b == 0 && threadIdx.x < kNumXcd) ws.ctrl[8 + threadIdx.x] = 0;   // the work queues
@@ -77,13 +77,12 @@ __global__ __launch_bounds__(kExtendThreads) void plan_extend_kernel(
     int code = 0;
     if (j < batch) code = extend_check(j, nexus_cu, keep_len, body_len, cache_len, row_cap, max_rows, total_new, &r);
     const int nb = (r.cost > own.cost || (r.cost == own.cost && j < b)) ? r.nt : 0;
-    int t0, t1, t2;
-    block_int_scan<kExtendThreads>(nb, &t0, lds);
-    block_int_scan<kExtendThreads>(r.nt, &t1, lds);
-    block_int_scan<kExtendThreads>(code != 0 ? 1 : 0, &t2, lds);
-    before += t0;
-    all += t1;
-    nbad += t2;
+    const int x[3] = {nb, r.nt, code != 0 ? 1 : 0};
+    int below[3], total[3];
+    block_int_scan_n<kExtendThreads, 3>(x, below, total, lds);
+    before += total[0];
+    all += total[1];
+    nbad += total[2];
   }
   if (own_code != 0 && clear && threadIdx.x == 0) raise_status(status, own_code);
   if (!clear || nbad > 0) {

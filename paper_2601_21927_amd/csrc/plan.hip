@@ -35,26 +35,21 @@ constexpr int kCostBuckets = 1024;
 // One step of the grammar SYSTEM* (TEXT+ NEXUS*)* CURRENT* of Eq.(1): may a token
 // with role r and segment id t follow one with role rp and id tp (rp = -1 at the
 // first token of a request)?  Segment ids are constant within a segment and
-// strictly increase between segments.
+// strictly increase between segments.  Per pair of roles, which orders of the ids are
+// allowed (1: t < tp, 2: equal, 4: t > tp), packed in one word: as branches for each of a
+// thread's eight tokens the grammar was most of the kernel's code.
+constexpr uint64_t allow(int rp, int r, int orders) { return static_cast<uint64_t>(orders) << (3 * (4 * (rp + 1) + r)); }
+constexpr uint64_t kGrammar =
+    allow(-1, kSystem, 7) | allow(-1, kText, 7) | allow(-1, kCurrent, 7) |
+    allow(kSystem, kSystem, 7) | allow(kSystem, kText, 7) | allow(kSystem, kCurrent, 7) |
+    allow(kText, kText, 6) | allow(kText, kNexus, 2) | allow(kText, kCurrent, 7) |
+    allow(kNexus, kNexus, 2) | allow(kNexus, kText, 4) | allow(kNexus, kCurrent, 7) |
+    allow(kCurrent, kCurrent, 7);
+static_assert(kSystem == 0 && kText == 1 && kNexus == 2 && kCurrent == 3, "roles index the grammar");
 __device__ __forceinline__ bool legal_step(int rp, int tp, int r, int t) {
-  if (r < kSystem || r > kCurrent) return false;
-  switch (rp) {
-    case -1:
-    case kSystem:
-      return r != kNexus;
-    case kText:
-      if (r == kText) return t >= tp;
-      if (r == kNexus) return t == tp;
-      return r == kCurrent;
-    case kNexus:
-      if (r == kNexus) return t == tp;
-      if (r == kText) return t > tp;
-      return r == kCurrent;
-    case kCurrent:
-      return r == kCurrent;
-    default:
-      return false;
-  }
+  const int order = t < tp ? 1 : (t == tp ? 2 : 4);
+  const int i = 4 * (rp + 1) + r;
+  return r <= kCurrent && rp <= kCurrent && ((kGrammar >> (3 * (i & 31) & 63)) & order) != 0;
 }
 
 // One workgroup per request: validate, list the Nexus positions and the runs,
@@ -64,10 +59,13 @@ __global__ __launch_bounds__(kPlanThreads) void plan_runs_kernel(const int32_t *
                                                                  const int32_t *__restrict__ turn, PrefillWs ws,
                                                                  int total_tokens, int nexus_scope,
                                                                  int32_t *status) {
-  __shared__ int lds[kPlanThreads / kWave + 1];
+  __shared__ int lds[kPlanThreads / kWave];
   __shared__ int lds4[4 * (kPlanThreads / kWave)];
+  __shared__ int4 s_run[kPlanThreads];
+  __shared__ int s_first[kPlanThreads];
   __shared__ unsigned long long s_cost;
   const int b = blockIdx.x;
+  if (threadIdx.x == 0) s_cost = 0ull;
   const int s = cu[b];
   const int e = cu[b + 1];
   if (s < 0 || e < s || e > total_tokens) {   // cu_seqlens itself is malformed
@@ -87,59 +85,83 @@ __global__ __launch_bounds__(kPlanThreads) void plan_runs_kernel(const int32_t *
   // block scan places its entries, and a second walk over its registers writes
   // them.  A token's predecessor is the thread's previous token, or the lower
   // lane's last one (lane 0 loads its own).
+  // The next chunk's tokens are requested before this one's are looked at.
   int pre_carry = 0, run_carry = 0, nexus_count = 0, bad_count = 0;
   const int lane = threadIdx.x % kWave;
-  for (int base = 0; base < L; base += kPlanThreads * kPlanTok) {
+  struct Tokens {
+    int r[kPlanTok], t[kPlanTok], rp, tp;   // roles and ids; those before the first (lane 0)
+  };
+  auto load = [&](int base, Tokens &k) {
     const int i0 = base + threadIdx.x * kPlanTok;
-    int r[kPlanTok], t[kPlanTok];
+    static_assert(kPlanTok == 8, "one 8-byte and two 16-byte loads");
+    if (i0 + kPlanTok <= L) {
+      uint64_t rr;
+      u32x4 ta, tb;
+      __builtin_memcpy(&rr, role + s + i0, 8);
+      __builtin_memcpy(&ta, turn + s + i0, 16);
+      __builtin_memcpy(&tb, turn + s + i0 + 4, 16);
+#pragma unroll
+      for (int j = 0; j < kPlanTok; ++j) {
+        k.r[j] = static_cast<int>((rr >> (8 * j)) & 0xFF);
+        k.t[j] = static_cast<int>(j < 4 ? ta[j & 3] : tb[j & 3]);
+      }
+    } else {
+#pragma unroll
+      for (int j = 0; j < kPlanTok; ++j) {
+        k.r[j] = -1;
+        k.t[j] = 0;
+        if (i0 + j < L) {
+          k.r[j] = role[s + i0 + j];
+          k.t[j] = turn[s + i0 + j];
+        }
+      }
+    }
+    k.rp = -1;
+    k.tp = 0;
+    if (lane == 0 && i0 > 0 && i0 <= L) {
+      k.rp = role[s + i0 - 1];
+      k.tp = turn[s + i0 - 1];
+    }
+  };
+  Tokens cur, ahead;
+  constexpr int kChunk = kPlanThreads * kPlanTok;
+  for (int base = -kChunk; base < L; base += kChunk, cur = ahead) {
+    if (base + kChunk < L) load(base + kChunk, ahead);
+    if (base < 0) continue;
+    const int i0 = base + threadIdx.x * kPlanTok;
+    const int(&r)[kPlanTok] = cur.r, (&t)[kPlanTok] = cur.t;
+    int rp = __shfl_up(r[kPlanTok - 1], 1), tp = __shfl_up(t[kPlanTok - 1], 1);
+    if (lane == 0) {
+      rp = cur.rp;
+      tp = cur.tp;
+    }
+    // bit j: token j is a prefix row, starts a run, is a Nexus token, breaks the grammar
+    uint32_t pre = 0, start = 0, nexus = 0, bad = 0;
 #pragma unroll
     for (int j = 0; j < kPlanTok; ++j) {
-      r[j] = -1;
-      t[j] = 0;
-      if (i0 + j < L) {
-        r[j] = role[s + i0 + j];
-        t[j] = turn[s + i0 + j];
-      }
+      const uint32_t in = i0 + j < L ? 1u << j : 0u;
+      pre |= (r[j] == kSystem || r[j] == kNexus) ? in : 0u;
+      start |= (i0 + j == 0 || r[j] != rp || (r[j] == kText && t[j] != tp)) ? in : 0u;
+      nexus |= r[j] == kNexus ? in : 0u;
+      bad |= legal_step(rp, tp, r[j], t[j]) ? 0u : in;
+      rp = r[j];
+      tp = t[j];
     }
-    int rp0 = __shfl_up(r[kPlanTok - 1], 1), tp0 = __shfl_up(t[kPlanTok - 1], 1);
-    if (lane == 0) {
-      rp0 = -1;
-      tp0 = 0;
-      if (i0 > 0 && i0 <= L) {
-        rp0 = role[s + i0 - 1];
-        tp0 = turn[s + i0 - 1];
-      }
-    }
-    int cnt[4] = {0, 0, 0, 0};   // prefix rows, run starts, Nexus tokens, illegal steps
-    {
-      int rp = rp0, tp = tp0;
-#pragma unroll
-      for (int j = 0; j < kPlanTok; ++j) {
-        if (i0 + j < L) {
-          cnt[0] += (r[j] == kSystem || r[j] == kNexus) ? 1 : 0;
-          cnt[1] += (i0 + j == 0 || r[j] != rp || (r[j] == kText && t[j] != tp)) ? 1 : 0;
-          cnt[2] += r[j] == kNexus ? 1 : 0;
-          cnt[3] += legal_step(rp, tp, r[j], t[j]) ? 0 : 1;
-        }
-        rp = r[j];
-        tp = t[j];
-      }
-    }
+    const int cnt[4] = {static_cast<int>(__popc(pre)), static_cast<int>(__popc(start)), static_cast<int>(__popc(nexus)),
+                        static_cast<int>(__popc(bad))};
     int below[4], tot[4];
     block_int_scan_n<kPlanThreads, 4>(cnt, below, tot, lds4);
-    {
-      int rp = rp0, tp = tp0;
-      int pc = pre_carry + below[0], rc = run_carry + below[1];
+    const int pc0 = pre_carry + below[0], rc0 = run_carry + below[1];
 #pragma unroll
-      for (int j = 0; j < kPlanTok; ++j) {
-        const int i = i0 + j;
-        if (i < L) {
-          if (i == 0 || r[j] != rp || (r[j] == kText && t[j] != tp)) ws.runs[s + rc++] = make_int2(i, pc);
-          if (r[j] == kSystem || r[j] == kNexus) ws.prefix_pos[s + pc++] = i;
-        }
-        rp = r[j];
-        tp = t[j];
+    for (int j = 0; j < kPlanTok; ++j) {
+      const uint32_t lower = (1u << j) - 1u;
+      const int pc = pc0 + __popc(pre & lower);
+      if ((start >> j) & 1) {
+        const int rc = rc0 + __popc(start & lower);
+        ws.runs[s + rc] = make_int2(i0 + j, pc);
+        if (rc < kPlanThreads) s_run[rc] = make_int4(i0 + j, pc, r[j], 0);
       }
+      if ((pre >> j) & 1) ws.prefix_pos[s + pc] = i0 + j;
     }
     pre_carry += tot[0];
     run_carry += tot[1];
@@ -156,67 +178,75 @@ __global__ __launch_bounds__(kPlanThreads) void plan_runs_kernel(const int32_t *
   }
   const int nruns = run_carry;
   const int k_tot = nexus_count;
+  // run i: start, prefix rows before it, role; the first kPlanThreads runs are in LDS
+  auto run_at = [&](int i) {
+    if (i < kPlanThreads) return s_run[i];
+    const int2 x = ws.runs[s + i];
+    return make_int4(x.x, x.y, role[s + x.x], 0);
+  };
   int S = 0;
-  if (L > 0 && role[s] == kSystem) S = nruns > 1 ? ws.runs[s + 1].x : L;
+  if (L > 0 && s_run[0].z == kSystem) S = nruns > 1 ? s_run[1].x : L;
   const int npre_all = S + k_tot;
-  if (threadIdx.x == 0) s_cost = 0ull;
 
-  // Pass 2: descriptors, run by run.
+  // Pass 2: descriptors.  A thread sizes one run, then the threads share the blocks of
+  // these runs and find each one's run in the list of first blocks.
   int tile_carry = 0;
+  int64_t cost = 0;
   for (int rb = 0; rb < nruns; rb += kPlanThreads) {
-    const int r = rb + threadIdx.x;
-    const bool in = r < nruns;
-    int start = 0, end = 0, nt = 0;
-    if (in) {
-      start = ws.runs[s + r].x;
-      end = (r + 1 < nruns) ? ws.runs[s + r + 1].x : L;
-      nt = (end - start + kTileRows - 1) / kTileRows;
+    const int cnt = min(kPlanThreads, nruns - rb);
+    int nt = 0;
+    if (threadIdx.x < cnt) {
+      const int r = rb + threadIdx.x;
+      nt = ((r + 1 < nruns ? run_at(r + 1).x : L) - run_at(r).x + kTileRows - 1) / kTileRows;
     }
     int ttot;
-    const int toff = block_int_scan<kPlanThreads>(nt, &ttot, lds);
-    if (in) {
-      const int kind = role[s + start];
-      const int pre_before = ws.runs[s + r].y;
-      int body_start = 0, body_len = 0;
-      if (kind == kNexus) {  // the grammar puts the owning body run right before
-        body_start = ws.runs[s + r - 1].x;
-        body_len = start - body_start;
+    s_first[threadIdx.x] = block_int_scan<kPlanThreads>(nt, &ttot, lds);
+    __syncthreads();
+    for (int i = threadIdx.x; i < ttot; i += kPlanThreads) {
+      int lo = 0, hi = cnt;   // s_first[lo] <= i < s_first[hi]; every run has a block
+      while (hi - lo > 1) {
+        const int mid = (lo + hi) / 2;
+        if (s_first[mid] <= i) lo = mid;
+        else hi = mid;
       }
-      unsigned long long my_cost = 0;
-      for (int j = 0; j < nt; ++j) {
-        TileDesc d;
-        d.req = b;
-        d.p0 = start + j * kTileRows;
-        d.nrows = min(kTileRows, end - d.p0);
-        d.pad = 0;
-        if (kind == kSystem) {          // system rows before the block, then the block
-          d.npre = d.p0;
-          d.seg_start = d.p0;
-          d.seg_len = d.nrows;
-          d.ndiag = d.nrows;
-        } else if (kind == kText) {     // system + earlier Nexus, own body up to the block
-          d.npre = pre_before;
-          d.seg_start = start;
-          d.seg_len = d.p0 + d.nrows - start;
-          d.ndiag = d.nrows;
-        } else if (kind == kNexus) {    // system + every Nexus (or up to its own), the owning body
-          d.npre = nexus_scope == SONIC_NEXUS_ALL ? npre_all : pre_before + (end - start);
-          d.seg_start = body_start;
-          d.seg_len = body_len;
-          d.ndiag = 0;
-        } else {                        // system + every Nexus, current query up to the block
-          d.npre = npre_all;
-          d.seg_start = start;
-          d.seg_len = d.p0 + d.nrows - start;
-          d.ndiag = d.nrows;
-        }
-        ws.tiles[s + tile_carry + toff + j] = d;
-        my_cost += static_cast<unsigned long long>(tile_cost(d));
+      const int r = rb + lo;
+      const int4 run = run_at(r);
+      const int start = run.x, pre_before = run.y, kind = run.z;
+      const int end = r + 1 < nruns ? run_at(r + 1).x : L;
+      TileDesc d;
+      d.req = b;
+      d.p0 = start + (i - s_first[lo]) * kTileRows;
+      d.nrows = min(kTileRows, end - d.p0);
+      d.pad = 0;
+      if (kind == kSystem) {          // system rows before the block, then the block
+        d.npre = d.p0;
+        d.seg_start = d.p0;
+        d.seg_len = d.nrows;
+        d.ndiag = d.nrows;
+      } else if (kind == kText) {     // system + earlier Nexus, own body up to the block
+        d.npre = pre_before;
+        d.seg_start = start;
+        d.seg_len = d.p0 + d.nrows - start;
+        d.ndiag = d.nrows;
+      } else if (kind == kNexus) {    // system + every Nexus (or up to its own), the owning body:
+        const int body = run_at(r - 1).x;   // the grammar puts its run right before
+        d.npre = nexus_scope == SONIC_NEXUS_ALL ? npre_all : pre_before + (end - start);
+        d.seg_start = body;
+        d.seg_len = start - body;
+        d.ndiag = 0;
+      } else {                        // system + every Nexus, current query up to the block
+        d.npre = npre_all;
+        d.seg_start = start;
+        d.seg_len = d.p0 + d.nrows - start;
+        d.ndiag = d.nrows;
       }
-      if (my_cost) atomicAdd(&s_cost, my_cost);
+      ws.tiles[s + tile_carry + i] = d;
+      cost += tile_cost(d);
     }
     tile_carry += ttot;
+    __syncthreads();   // s_first is rewritten
   }
+  if (cost > 0) atomicAdd(&s_cost, static_cast<unsigned long long>(cost));
   __syncthreads();
   if (threadIdx.x == 0) ws.req[b] = ReqInfo{tile_carry, S, k_tot, nruns, static_cast<int64_t>(s_cost), 0};
 }
@@ -227,15 +257,10 @@ __global__ __launch_bounds__(kPlanThreads) void plan_runs_kernel(const int32_t *
 // index), so that first slot is the number of descriptors of the requests ranked
 // before it: a workgroup sum over the batch, no global sort.  Workgroup 0 also
 // writes the descriptor count and resets the queues.
-__global__ __launch_bounds__(kPlanThreads) void plan_order_kernel(int batch, const int32_t *__restrict__ cu,
-                                                                  PrefillWs ws, const int32_t *status) {
-  __shared__ int hist[kCostBuckets];
-  __shared__ int lds[kPlanThreads / kWave + 1];
-  __shared__ int s_ok;
+__device__ __forceinline__ void plan_order(int b, bool ok, int batch, const int32_t *__restrict__ cu, const PrefillWs &ws,
+                                           int *hist, int *lds) {
   static_assert(kCostBuckets == kPlanThreads, "one histogram bucket per thread");
-  const int b = blockIdx.x;
   hist[threadIdx.x] = 0;
-  const bool ok = block_status_clear(status, &s_ok);
   if (b == 0 && threadIdx.x < kNumXcd) ws.ctrl[8 + threadIdx.x] = 0;
   if (!ok) {
     if (b == 0 && threadIdx.x == 0) ws.ctrl[0] = 0;
@@ -251,16 +276,17 @@ __global__ __launch_bounds__(kPlanThreads) void plan_order_kernel(int batch, con
       nt_j = rj.ntiles;
       nb = (rj.cost > cb || (rj.cost == cb && j < b)) ? nt_j : 0;
     }
-    int t0, t1;
-    block_int_scan<kPlanThreads>(nb, &t0, lds);
-    block_int_scan<kPlanThreads>(nt_j, &t1, lds);
-    before += t0;
-    all += t1;
+    const int x[2] = {nb, nt_j};
+    int below[2], total[2];
+    block_int_scan_n<kPlanThreads, 2>(x, below, total, lds);
+    before += total[0];
+    all += total[1];
   }
   if (b == 0 && threadIdx.x == 0) ws.ctrl[0] = all;
   const int nt = ws.req[b].ntiles;
   const int base = cu[b];
   const int dst = before;
+  __syncthreads();   // hist is clear
   for (int j = threadIdx.x; j < nt; j += kPlanThreads) {
     const int c = min(tile_cost(ws.tiles[base + j]), kCostBuckets - 1);
     atomicAdd(&hist[kCostBuckets - 1 - c], 1);
@@ -283,20 +309,13 @@ __global__ __launch_bounds__(kPlanThreads) void plan_order_kernel(int batch, con
 // prefix.  The wave's first lanes read the rows' positions, then every
 // lane has all of its 16-byte pieces of those rows in flight before it stores
 // (kGatherPieces per row and tensor at a time).
-constexpr int kGatherThreads = 256;
-constexpr int kGatherWaves = kGatherThreads / kWave;
+constexpr int kGatherWaves = kPlanThreads / kWave;
 constexpr int kGatherRows = 4;
 constexpr int kGatherPieces = 2;
 
-__global__ __launch_bounds__(kGatherThreads) void gather_prefix_kernel(const int32_t *__restrict__ cu,
-                                                                      const uint16_t *__restrict__ k,
-                                                                      const uint16_t *__restrict__ v, PrefillWs ws,
-                                                                      int row_pieces, int gx,
-                                                                      const int32_t *status) {
-  __shared__ int s_ok;
-  if (!block_status_clear(status, &s_ok)) return;
-  const int b = blockIdx.x / gx;
-  const int bx = blockIdx.x % gx;
+__device__ __forceinline__ void gather_prefix(int b, int bx, int gx, const int32_t *__restrict__ cu,
+                                              const uint16_t *__restrict__ k, const uint16_t *__restrict__ v,
+                                              const PrefillWs &ws, int row_pieces) {
   const int s0 = cu[b];
   const ReqInfo ri = ws.req[b];
   const int npre = ri.system + ri.nexus_total;
@@ -340,11 +359,20 @@ __global__ __launch_bounds__(kGatherThreads) void gather_prefix_kernel(const int
   }
 }
 
-// Work order of the prefill's descriptors (request b's at offset cu[b] of ws.tiles)
-// and reset queues.
-hipError_t launch_plan_order(int batch, const int32_t *cu, PrefillWs ws, int32_t *status, hipStream_t stream) {
-  plan_order_kernel<<<dim3(batch), dim3(kPlanThreads), 0, stream>>>(batch, cu, ws, status);
-  return hipGetLastError();
+// Both need only the run kernel's results: workgroups [0, batch) order a request's
+// descriptors, the others copy prefixes (one launch after the other, the order took 6 us
+// of its own before a copy of 19).
+__global__ __launch_bounds__(kPlanThreads) void plan_finish_kernel(int batch, const int32_t *__restrict__ cu,
+                                                                   const uint16_t *__restrict__ k,
+                                                                   const uint16_t *__restrict__ v, PrefillWs ws,
+                                                                   int row_pieces, int gx, const int32_t *status) {
+  __shared__ int hist[kCostBuckets];
+  __shared__ int lds[2 * (kPlanThreads / kWave)];
+  __shared__ int s_ok;
+  const bool ok = block_status_clear(status, &s_ok);
+  const int w = static_cast<int>(blockIdx.x) - batch;
+  if (w < 0) plan_order(blockIdx.x, ok, batch, cu, ws, hist, lds);
+  else if (ok) gather_prefix(w / gx, w % gx, gx, cu, k, v, ws, row_pieces);
 }
 
 // Grammar check and run table only (ws.req, ws.prefix_pos, ws.runs; ws.tiles is
@@ -361,15 +389,15 @@ hipError_t launch_plan(int batch, int total_tokens, int Hkv, int D, int nexus_sc
                        int32_t *status, hipStream_t stream) {
   plan_runs_kernel<<<dim3(batch), dim3(kPlanThreads), 0, stream>>>(cu, role, turn, ws, total_tokens, nexus_scope,
                                                                     status);
-  hipError_t e = launch_plan_order(batch, cu, ws, status, stream);
+  hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   const int row_pieces = Hkv * D / 8;
-  // about 2048 workgroups over the batch, none with nothing but rows past every prefix
+  // about two workgroups per CU over the batch, none with nothing but rows past every prefix
   constexpr int rows_per_block = kGatherWaves * kGatherRows;
   const int by_rows = (total_tokens + rows_per_block - 1) / rows_per_block;
-  const int gx = max(1, min((2048 + batch - 1) / batch, by_rows));
-  gather_prefix_kernel<<<dim3(gx * batch), dim3(kGatherThreads), 0, stream>>>(cu, k, v, ws, row_pieces, gx,
-                                                                              status);
+  const int gx = max(1, min((512 + batch - 1) / batch, by_rows));
+  plan_finish_kernel<<<dim3(batch + gx * batch), dim3(kPlanThreads), 0, stream>>>(batch, cu, k, v, ws, row_pieces, gx,
+                                                                                  status);
   return hipGetLastError();
 }
 

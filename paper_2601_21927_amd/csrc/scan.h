@@ -1,4 +1,4 @@
-// Workgroup-wide prefix sums built from wave ballots (flags) and wave shuffles (integers).
+// Workgroup-wide prefix sums built from wave ballots (flags) and lane shifts (integers).
 #pragma once
 
 #include "common.h"
@@ -9,6 +9,18 @@ namespace sonic {
 __device__ __forceinline__ int lanes_below(uint64_t mask) {
   return __builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(mask >> 32),
                                    __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(mask), 0));
+}
+
+// Inclusive sum over the lanes of a wave, without LDS round trips: four shifts inside the
+// rows of 16 lanes, then the rows' totals broadcast to the rows behind.
+__device__ __forceinline__ int wave_scan(int x) {
+  x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xF, 0xF, false);   // row_shr:1
+  x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xF, 0xF, false);   // row_shr:2
+  x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xF, 0xF, false);   // row_shr:4
+  x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xF, 0xF, false);   // row_shr:8
+  x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xA, 0xF, false);   // row_bcast:15 into rows 1 and 3
+  x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xC, 0xF, false);   // row_bcast:31 into rows 2 and 3
+  return x;
 }
 
 // Exclusive prefix count of a 0/1 flag over an NT-thread workgroup.
@@ -48,15 +60,7 @@ __device__ __forceinline__ void block_int_scan_n(const int (&x)[NV], int (&below
   const int w = threadIdx.x / kWave;
   int v[NV];
 #pragma unroll
-  for (int f = 0; f < NV; ++f) v[f] = x[f];
-#pragma unroll
-  for (int o = 1; o < kWave; o <<= 1) {
-#pragma unroll
-    for (int f = 0; f < NV; ++f) {
-      const int y = __shfl_up(v[f], o);
-      if (lane >= o) v[f] += y;
-    }
-  }
+  for (int f = 0; f < NV; ++f) v[f] = wave_scan(x[f]);
   if (lane == kWave - 1)
 #pragma unroll
     for (int f = 0; f < NV; ++f) lds[f * NW + w] = v[f];
@@ -76,34 +80,14 @@ __device__ __forceinline__ void block_int_scan_n(const int (&x)[NV], int (&below
   lds_barrier();
 }
 
-// Exclusive prefix sum of a non-negative int over an NT-thread workgroup.
+// Exclusive prefix sum of an int over an NT-thread workgroup.
 template <int NT>
 __device__ __forceinline__ int block_int_scan(int x, int *total, int *lds) {
-  constexpr int NW = NT / kWave;
-  const int lane = threadIdx.x & (kWave - 1);
-  const int w = threadIdx.x / kWave;
-  int v = x;
-#pragma unroll
-  for (int o = 1; o < kWave; o <<= 1) {
-    const int y = __shfl_up(v, o);
-    if (lane >= o) v += y;
-  }
-  if (lane == kWave - 1) lds[w] = v;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    int run = 0;
-    for (int i = 0; i < NW; ++i) {
-      const int c = lds[i];
-      lds[i] = run;
-      run += c;
-    }
-    lds[NW] = run;
-  }
-  __syncthreads();
-  const int res = lds[w] + v - x;
-  *total = lds[NW];
-  __syncthreads();
-  return res;
+  const int v[1] = {x};
+  int below[1], tot[1];
+  block_int_scan_n<NT, 1>(v, below, tot, lds);
+  *total = tot[0];
+  return below[0];
 }
 
 }  // namespace sonic

@@ -222,3 +222,20 @@ def test_prefill_default_scale_is_one_over_sqrt_d():
         assert db.read_status() == 0
         outs.append(db.out.cpu().numpy())
     assert np.array_equal(outs[0], outs[1])
+
+
+def test_prefill_many_runs():
+    """More runs than the planner keeps on chip and more tokens than one pass of it takes."""
+    H.need_gpu()
+    lays = [W.RequestLayout(3, [5] * 1400, [1] * 1400, 40), W.RequestLayout(0, [9, 700], [0, 33], 1)]
+    assert lays[0].length > 8192
+    batch = W.make_batch("runs", lays, 4, 2, 64, seed=77)
+    db = H.device_batch(batch)
+    assert db.prefill() == sonic.OK
+    torch.cuda.synchronize()
+    assert db.read_status() == 0
+    got = db.out.cpu().numpy()
+    rng = np.random.default_rng(7)
+    rows = [np.unique(np.concatenate([rng.integers(0, lay.length, 150), np.arange(lay.length - 50, lay.length)])) for lay in lays]
+    for b, want in enumerate(H.oracle_prefill_rows(batch, rows)):
+        H.assert_close(got[int(batch.cu_seqlens[b]) + rows[b]], want, f"request {b}")

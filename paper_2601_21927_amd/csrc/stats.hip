@@ -58,7 +58,7 @@ __global__ __launch_bounds__(kStatThreads) void stats_plan_kernel(int batch, con
 template <int D> __device__ __forceinline__ int swz_w(int m) { return m & (D / 8 - 1); }
 
 template <int D, int G>
-__global__ __launch_bounds__(G * kWave) void key_weight_kernel(const int32_t *__restrict__ cu,
+__global__ __launch_bounds__(G * kWave, 3) void key_weight_kernel(const int32_t *__restrict__ cu,
                                                                const uint16_t *__restrict__ q,
                                                                const uint16_t *__restrict__ k, PrefillWs ws,
                                                                int Hkv, int T, float scale_log2) {
@@ -102,7 +102,8 @@ __global__ __launch_bounds__(G * kWave) void key_weight_kernel(const int32_t *__
 
     const int h = kvh * G + wave;
     f32x16 wacc[2] = {f32x16{}, f32x16{}};
-    for (int r0 = 0; r0 < C; r0 += 32) {
+    // rows before the block's first current key see none of it
+    for (int r0 = max(j0 - npre, 0) & ~31; r0 < C; r0 += 32) {
       const int r = r0 + n;   // current-query row of this lane's column
       const bool valid = r < C;
       const size_t qidx = static_cast<size_t>(s0 + L - C + (valid ? r : 0)) * Hq + h;
@@ -114,6 +115,7 @@ __global__ __launch_bounds__(G * kWave) void key_weight_kernel(const int32_t *__
         qf[ds] = __builtin_bit_cast(bf16x8, w);
       }
       const float lse = valid ? ws.lse[qidx] : INFINITY;
+      const int lim = npre + r + 1 - j0 - 4 * g;   // bound on the element's key, less j0 + 4 g
 #pragma unroll
       for (int kb = 0; kb < 2; ++kb) {
         f32x16 s = f32x16{};
@@ -123,11 +125,13 @@ __global__ __launch_bounds__(G * kWave) void key_weight_kernel(const int32_t *__
           const bf16x8 a = *reinterpret_cast<const bf16x8 *>(&k_lds[(m * DC + ((2 * ds + g) ^ swz_w<D>(m))) * 8]);
           s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, qf[ds], s, 0, 0, 0);
         }
-        // element e holds key 8 * (e / 4) + 4 * g + e % 4 of the 32-key block, row r
+        // Element e holds key 8 * (e / 4) + 4 * g + e % 4 of the 32-key block, row r.  A
+        // row sees the keys below npre + r + 1; one past the last has an infinite
+        // normaliser, its terms are zero.  So one comparison with a constant per element
+        // stands for the row's, the key's and the causal test.
 #pragma unroll
         for (int e = 0; e < 16; ++e) {
-          const int j = j0 + kb * 32 + 8 * (e >> 2) + 4 * g + (e & 3);
-          const bool vis = valid && j < nkeep && (j < npre || j - npre <= r);
+          const bool vis = kb * 32 + 8 * (e >> 2) + (e & 3) < lim;
           wacc[kb][e] += vis ? __builtin_amdgcn_exp2f(fmaf(s[e], scale_log2, -lse)) : 0.f;
         }
       }

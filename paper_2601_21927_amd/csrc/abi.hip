@@ -10,7 +10,8 @@
 #include "common.h"
 
 namespace sonic {
-hipError_t launch_plan(int batch, int total_tokens, int Hkv, int D, int nexus_scope, const int32_t *cu,
+int prefill_tile_rows(int G);
+hipError_t launch_plan(int batch, int total_tokens, int Hkv, int D, int nexus_scope, int tile_rows, const int32_t *cu,
                        const uint8_t *role, const int32_t *turn, const uint16_t *k, const uint16_t *v, PrefillWs ws,
                        int32_t *status, hipStream_t stream);
 hipError_t prefill_occupancy(int D, int G, bool stats, int ks, int *blocks);
@@ -36,7 +37,7 @@ hipError_t launch_extend_append(int batch, int max_new, int max_rows, int Hkv, i
                                 int32_t *cache_len, const uint16_t *k_new, const uint16_t *v_new, PrefillWs ws,
                                 const uint16_t *k_stage, const uint16_t *v_stage, const int32_t *status,
                                 hipStream_t stream);
-hipError_t launch_prefill(int D, int G, int grid, bool stats, int ks, AttnRows rows, PrefillWs ws, int Hkv, float scale_log2,
+hipError_t launch_prefill(int D, int G, int grid, bool stats, int ks, int tile_rows, AttnRows rows, PrefillWs ws, int Hkv, float scale_log2,
                           hipStream_t stream);
 hipError_t launch_compact(int batch, int total_tokens, int max_seqlen, int Hkv, int D, const int32_t *cu,
                           const uint8_t *role,
@@ -307,7 +308,7 @@ int32_t sonic_segment_attn_prefill(int32_t batch, int32_t total_tokens, int32_t 
   DeviceInfo *di = nullptr;
   hipError_t e = device_info(&di);
   if (e != hipSuccess) return SONIC_ERR_HIP;
-  e = launch_plan(batch, total_tokens, Hkv, d, nexus_scope, cu_seqlens, role, turn_id,
+  e = launch_plan(batch, total_tokens, Hkv, d, nexus_scope, prefill_tile_rows(G), cu_seqlens, role, turn_id,
                   static_cast<const uint16_t *>(k), static_cast<const uint16_t *>(v), ws, dev_status, stream);
   if (e != hipSuccess) return SONIC_ERR_HIP;
   const bool stats = nexus_mass != nullptr || key_weight != nullptr;
@@ -316,7 +317,7 @@ int32_t sonic_segment_attn_prefill(int32_t batch, int32_t total_tokens, int32_t 
   AttnRows rows{cu_seqlens, nullptr, static_cast<const uint16_t *>(q), static_cast<const uint16_t *>(k),
                 static_cast<const uint16_t *>(v), ws.k_pre, ws.v_pre, out, nexus_mass, ws.lse};
   const float scale_log2 = static_cast<float>(softmax_scale * kLog2e);
-  e = launch_prefill(d, G, grid, stats, 1, rows, ws, Hkv, scale_log2, stream);
+  e = launch_prefill(d, G, grid, stats, 1, prefill_tile_rows(G), rows, ws, Hkv, scale_log2, stream);
   if (e == hipSuccess && key_weight != nullptr)
     e = launch_key_weight(batch, total_tokens, Hq, Hkv, d, di->num_cus, cu_seqlens, role,
                           static_cast<const uint16_t *>(q), static_cast<const uint16_t *>(k), ws, scale_log2,
@@ -419,7 +420,7 @@ int32_t sonic_nexus_extend(int32_t batch, int32_t total_new, int32_t Hq, int32_t
     AttnRows rows{nexus_cu, cache_row_off, static_cast<const uint16_t *>(q), static_cast<const uint16_t *>(k),
                   static_cast<const uint16_t *>(v), static_cast<const uint16_t *>(k_cache),
                   static_cast<const uint16_t *>(v_cache), out};
-    e = launch_prefill(d, G, grid, false, ks, rows, ws, Hkv, static_cast<float>(softmax_scale * kLog2e), stream);
+    e = launch_prefill(d, G, grid, false, ks, kTileRows, rows, ws, Hkv, static_cast<float>(softmax_scale * kLog2e), stream);
     if (e != hipSuccess) return SONIC_ERR_HIP;
   }
   e = launch_extend_append(batch, total_new, max_rows, Hkv, d, nexus_cu, keep_len, static_cast<uint16_t *>(k_cache),

@@ -126,8 +126,8 @@ __device__ __forceinline__ float rounded_sum(const bf16x8 (&p)[N]) {
 __device__ __forceinline__ float bf16_lo(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float bf16_hi(uint32_t w) { return __uint_as_float(w & 0xFFFF0000u); }
 
-// Prefill work descriptor of one block of up to 32 query rows that share one
-// visible-key list.  Every list is two contiguous pieces:
+// Prefill work descriptor of one block of up to 32 query rows (a few such blocks of one run
+// where few q-heads share a kv-head) that share one visible-key list.  Every list is two contiguous pieces:
 //   prefix rows [0, npre)            of the request's prefix copy (system prompt,
 //                                    then its Nexus tokens in order); every row sees them
 //   positions [seg_start, seg_start + seg_len)

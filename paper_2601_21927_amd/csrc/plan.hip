@@ -53,11 +53,11 @@ __device__ __forceinline__ bool legal_step(int rp, int tp, int r, int t) {
 }
 
 // One workgroup per request: validate, list the Nexus positions and the runs,
-// then emit one descriptor per block of up to 32 rows of a run.
+// then emit one descriptor per block of up to tile_rows rows of a run.
 __global__ __launch_bounds__(kPlanThreads) void plan_runs_kernel(const int32_t *__restrict__ cu,
                                                                  const uint8_t *__restrict__ role,
                                                                  const int32_t *__restrict__ turn, PrefillWs ws,
-                                                                 int total_tokens, int nexus_scope,
+                                                                 int total_tokens, int nexus_scope, int tile_rows,
                                                                  int32_t *status) {
   __shared__ int lds[kPlanThreads / kWave];
   __shared__ int lds4[4 * (kPlanThreads / kWave)];
@@ -197,7 +197,7 @@ __global__ __launch_bounds__(kPlanThreads) void plan_runs_kernel(const int32_t *
     int nt = 0;
     if (threadIdx.x < cnt) {
       const int r = rb + threadIdx.x;
-      nt = ((r + 1 < nruns ? run_at(r + 1).x : L) - run_at(r).x + kTileRows - 1) / kTileRows;
+      nt = ((r + 1 < nruns ? run_at(r + 1).x : L) - run_at(r).x + tile_rows - 1) / tile_rows;
     }
     int ttot;
     s_first[threadIdx.x] = block_int_scan<kPlanThreads>(nt, &ttot, lds);
@@ -215,8 +215,8 @@ __global__ __launch_bounds__(kPlanThreads) void plan_runs_kernel(const int32_t *
       const int end = r + 1 < nruns ? run_at(r + 1).x : L;
       TileDesc d;
       d.req = b;
-      d.p0 = start + (i - s_first[lo]) * kTileRows;
-      d.nrows = min(kTileRows, end - d.p0);
+      d.p0 = start + (i - s_first[lo]) * tile_rows;
+      d.nrows = min(tile_rows, end - d.p0);
       d.pad = 0;
       if (kind == kSystem) {          // system rows before the block, then the block
         d.npre = d.p0;
@@ -380,15 +380,15 @@ __global__ __launch_bounds__(kPlanThreads) void plan_finish_kernel(int batch, co
 hipError_t launch_plan_runs(int batch, int total_tokens, const int32_t *cu, const uint8_t *role, const int32_t *turn,
                             PrefillWs ws, int32_t *status, hipStream_t stream) {
   plan_runs_kernel<<<dim3(batch), dim3(kPlanThreads), 0, stream>>>(cu, role, turn, ws, total_tokens,
-                                                                    SONIC_NEXUS_ALL, status);
+                                                                    SONIC_NEXUS_ALL, kTileRows, status);
   return hipGetLastError();
 }
 
-hipError_t launch_plan(int batch, int total_tokens, int Hkv, int D, int nexus_scope, const int32_t *cu,
+hipError_t launch_plan(int batch, int total_tokens, int Hkv, int D, int nexus_scope, int tile_rows, const int32_t *cu,
                        const uint8_t *role, const int32_t *turn, const uint16_t *k, const uint16_t *v, PrefillWs ws,
                        int32_t *status, hipStream_t stream) {
   plan_runs_kernel<<<dim3(batch), dim3(kPlanThreads), 0, stream>>>(cu, role, turn, ws, total_tokens, nexus_scope,
-                                                                    status);
+                                                                    tile_rows, status);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   const int row_pieces = Hkv * D / 8;

@@ -165,10 +165,15 @@ __device__ __forceinline__ void stage_tensor(uint16_t *lds_buf, const char *pre_
 // list is fully masked).  The second group then hands its (max, sum, O) to the
 // first through LDS, which merges them by log-sum-exp and stores the rows: one
 // resident workgroup per CU with twice the waves, instead of half the CUs idle.
-template <int D, int G, bool STATS, int KS>
-__global__ __launch_bounds__(G * kWave * KS, 3 - KS) void prefill_kernel(AttnRows rows, PrefillWs ws, int Hkv,
+// RB > 1 (few q-heads per kv-head): the workgroup takes RB blocks of 32 consecutive rows of a
+// run, G waves each, and all share the staged K/V; the descriptor covers the RB blocks and its
+// last rows' key list, blocks before them mask its end.  Two workgroups fill a CU's LDS, so
+// with one block and G = 1 a CU ran two waves: 8 conversations of 5.4k tokens, 8 / 8 heads of
+// 128, 1160 us with one block, 280 with four; 4 / 2 heads of 64, 123 with one, 105 with two.
+template <int D, int G, bool STATS, int KS, int RB>
+__global__ __launch_bounds__(G * RB * kWave * KS, 3 - KS) void prefill_kernel(AttnRows rows, PrefillWs ws, int Hkv,
                                                                         float scale_log2) {
-  static_assert(KS == 1 || (KS == 2 && !STATS), "the key split serves the attention output only");
+  static_assert(KS == 1 || (KS == 2 && !STATS && RB == 1), "the key split serves the attention output of single blocks only");
   const uint16_t *__restrict__ q = rows.q;
   float *__restrict__ out = rows.out;
   constexpr int DC = D / 8;              // 16-byte chunks per K/V row
@@ -192,8 +197,11 @@ __global__ __launch_bounds__(G * kWave * KS, 3 - KS) void prefill_kernel(AttnRow
 
   const int Hq = Hkv * G;
   const int wave_id = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);   // uniform: lets waves branch on it
+  constexpr int NW = G * RB;                            // waves that stage and share K/V
   const int grp = KS == 1 ? 0 : wave_id / G;          // key half (KS = 2)
-  const int wave = KS == 1 ? wave_id : wave_id % G;   // q-head within the kv-head's group
+  const int wave = KS == 1 ? wave_id : wave_id % G;
+  const int head = RB == 1 ? wave : wave % G;         // q-head within the kv-head's group
+  const int row_blk = RB == 1 ? 0 : 32 * (wave / G);  // first row of the wave's block in the item
   uint16_t *const kbuf0 = k_lds0[grp];
   uint16_t *const kbuf1 = k_lds1[grp];
   uint16_t *const vbuf0 = v_lds0[grp];
@@ -232,7 +240,7 @@ __global__ __launch_bounds__(G * kWave * KS, 3 - KS) void prefill_kernel(AttnRow
     t.ndiag = __builtin_amdgcn_readfirstlane(t.ndiag);
     const int base = rows.seg_row0[t.req];
     const int64_t pbase = rows.pre_row0 != nullptr ? rows.pre_row0[t.req] : static_cast<int64_t>(base);
-    const int h = kvh * G + wave;
+    const int h = kvh * G + head;
     const int nv = tile_key_count(t);
     const int nF = nv - t.ndiag;
     const int npre = t.npre;
@@ -255,19 +263,19 @@ __global__ __launch_bounds__(G * kWave * KS, 3 - KS) void prefill_kernel(AttnRow
     const int c_stop = c_first + nloc;
     auto stage_step = [&](int c) { return (KS == 1 || c < c_stop) ? c : max(c, nchunks); };
     auto stage_k = [&](int c, uint16_t *buf) {
-      stage_tensor<D, G, false>(buf, kpre, kreq, row_bytes, koff_lane, wave, lane, stage_step(c), nv, npre,
+      stage_tensor<D, NW, false>(buf, kpre, kreq, row_bytes, koff_lane, wave, lane, stage_step(c), nv, npre,
                                 seg_shift);
     };
     auto stage_v = [&](int c, uint16_t *buf) {
-      stage_tensor<D, G, true>(buf, vpre, vreq, row_bytes, voff_lane, wave, lane, stage_step(c), nv, npre,
+      stage_tensor<D, NW, true>(buf, vpre, vreq, row_bytes, voff_lane, wave, lane, stage_step(c), nv, npre,
                                seg_shift);
     };
 
     // Q^T fragments (B operand of S): lane (row n, half g) holds d = 16*ds + 8*g .. +7.
     bf16x8 qf[DS];
     {
-      const bool ok = n < t.nrows;
-      const uint16_t *qrow = q + (static_cast<size_t>(base + t.p0 + n) * Hq + h) * D;
+      const bool ok = row_blk + n < t.nrows;
+      const uint16_t *qrow = q + (static_cast<size_t>(base + t.p0 + row_blk + n) * Hq + h) * D;
 #pragma unroll
       for (int ds = 0; ds < DS; ++ds) {
         u32x4 w = {0u, 0u, 0u, 0u};
@@ -296,9 +304,9 @@ __global__ __launch_bounds__(G * kWave * KS, 3 - KS) void prefill_kernel(AttnRow
     // of step c the loads newer than K(c) are V(c) and K(c+1), and in its middle the
     // loads newer than V(c) are K(c+1) and V(c+1): both waits are "all but the 2 * NJ
     // most recent", the same at every step.
-    constexpr int NJ = ((kKeyChunk / (kWave / (D / 8))) + G - 1) / G;
+    constexpr int NJ = ((kKeyChunk / (kWave / (D / 8))) + NW - 1) / NW;
     static_assert(2 * NJ < 64, "the wait count fits vmcnt");
-    __builtin_assume(wave < G);
+    __builtin_assume(wave < NW);
     auto step = [&](int c, uint16_t *kc_lds, const uint16_t *vc_lds, uint16_t *vn_lds) {
       wait_vm<2 * NJ>();
       lds_barrier();                                   // K(c) in LDS; every wave is past P.V(c - 1)
@@ -326,9 +334,9 @@ __global__ __launch_bounds__(G * kWave * KS, 3 - KS) void prefill_kernel(AttnRow
       // ---- mask (ragged end / causal diagonal only), online softmax ----
       if (vk0 + kKeyChunk > nF) {
         // Row n sees every key before the diagonal block and diagonal keys j <= n:
-        // virtual key vk is visible iff vk < min(nv, nF + n + 1).  One compare and a
+        // virtual key vk is visible iff vk < min(nv, nF + n + 1) (n counted in the item).  One compare and a
         // select per element, no divergent branches.
-        const int lim_g = min(nv, nF + n + 1) - vk0 - 8 * g;   // bound on acc_key0
+        const int lim_g = min(nv, nF + row_blk + n + 1) - vk0 - 8 * g;   // bound on acc_key0
 #pragma unroll
         for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
@@ -462,14 +470,14 @@ __global__ __launch_bounds__(G * kWave * KS, 3 - KS) void prefill_kernel(AttnRow
     if (STATS) {
       const float n_tot = pair32_add(l_nex);
       const float x_tot = pair32_add(l_ex);
-      if (n < t.nrows && g == 0) {
-        const size_t idx = static_cast<size_t>(base + t.p0 + n) * Hq + h;
+      if (row_blk + n < t.nrows && g == 0) {
+        const size_t idx = static_cast<size_t>(base + t.p0 + row_blk + n) * Hq + h;
         if (rows.nexus_mass != nullptr) rows.nexus_mass[idx] = n_tot / x_tot;
         rows.lse[idx] = m_run + __builtin_amdgcn_logf(x_tot);
       }
     }
-    if (n < t.nrows) {
-      float *orow = out + (static_cast<size_t>(base + t.p0 + n) * Hq + h) * D;
+    if (row_blk + n < t.nrows) {
+      float *orow = out + (static_cast<size_t>(base + t.p0 + row_blk + n) * Hq + h) * D;
 #pragma unroll
       for (int db = 0; db < DB; ++db) {
 #pragma unroll
@@ -712,37 +720,58 @@ __global__ __launch_bounds__(G * kWave, 2) void prefill_pp_kernel(AttnRows rows,
   }
 }
 
-template <int D, int G>
-static hipError_t launch_prefill_dg(int grid, bool stats, int ks, AttnRows rows, PrefillWs ws, int Hkv,
-                                    float scale_log2, hipStream_t stream) {
+// Blocks of 32 rows per workgroup of the prefill: four waves where one block has fewer.
+constexpr int row_blocks(int G) { return G == 1 ? 4 : (G == 2 ? 2 : 1); }
+int prefill_tile_rows(int G) { return kTileRows * row_blocks(G); }
+
+template <int D, int G, int RB>
+static hipError_t launch_prefill_rb(int grid, bool stats, AttnRows rows, PrefillWs ws, int Hkv, float scale_log2,
+                                    hipStream_t stream) {
   if (stats)
-    prefill_kernel<D, G, true, 1><<<dim3(grid), dim3(G * kWave), 0, stream>>>(rows, ws, Hkv, scale_log2);
-  else if (ks == 2) {
-    if constexpr (G <= 4)
-      prefill_kernel<D, G, false, 2><<<dim3(grid), dim3(2 * G * kWave), 0, stream>>>(rows, ws, Hkv, scale_log2);
-    else
-      return hipErrorInvalidValue;
-  } else if constexpr (G > 4)
+    prefill_kernel<D, G, true, 1, RB><<<dim3(grid), dim3(G * RB * kWave), 0, stream>>>(rows, ws, Hkv, scale_log2);
+  else if constexpr (G > 4)
     prefill_pp_kernel<D, G><<<dim3(grid), dim3(G * kWave), 0, stream>>>(rows, ws, Hkv, scale_log2);
   else
-    prefill_kernel<D, G, false, 1><<<dim3(grid), dim3(G * kWave), 0, stream>>>(rows, ws, Hkv, scale_log2);
+    prefill_kernel<D, G, false, 1, RB><<<dim3(grid), dim3(G * RB * kWave), 0, stream>>>(rows, ws, Hkv, scale_log2);
   return hipGetLastError();
+}
+
+// tile_rows: rows per descriptor of the plan, prefill_tile_rows(G) or kTileRows
+template <int D, int G>
+static hipError_t launch_prefill_dg(int grid, bool stats, int ks, int tile_rows, AttnRows rows, PrefillWs ws, int Hkv,
+                                    float scale_log2, hipStream_t stream) {
+  if (ks == 2) {
+    if constexpr (G <= 4) {
+      prefill_kernel<D, G, false, 2, 1><<<dim3(grid), dim3(2 * G * kWave), 0, stream>>>(rows, ws, Hkv, scale_log2);
+      return hipGetLastError();
+    } else {
+      return hipErrorInvalidValue;
+    }
+  }
+  if constexpr (row_blocks(G) > 1) {
+    if (tile_rows == kTileRows && !stats) {
+      prefill_kernel<D, G, false, 1, 1><<<dim3(grid), dim3(G * kWave), 0, stream>>>(rows, ws, Hkv, scale_log2);
+      return hipGetLastError();
+    }
+  }
+  return launch_prefill_rb<D, G, row_blocks(G)>(grid, stats, rows, ws, Hkv, scale_log2, stream);
 }
 
 template <int D, int G>
 static hipError_t occupancy_dg(bool stats, int ks, int *blocks) {
+  constexpr int RB = row_blocks(G);
   if (stats)
-    return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks, prefill_kernel<D, G, true, 1>, G * kWave, 0);
+    return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks, prefill_kernel<D, G, true, 1, RB>, G * RB * kWave, 0);
   if (ks == 2) {
     if constexpr (G <= 4)
-      return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks, prefill_kernel<D, G, false, 2>, 2 * G * kWave, 0);
+      return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks, prefill_kernel<D, G, false, 2, 1>, 2 * G * kWave, 0);
     else
       return hipErrorInvalidValue;
   }
   if constexpr (G > 4)
     return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks, prefill_pp_kernel<D, G>, G * kWave, 0);
   else
-    return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks, prefill_kernel<D, G, false, 1>, G * kWave, 0);
+    return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks, prefill_kernel<D, G, false, 1, RB>, G * RB * kWave, 0);
 }
 
 #define SONIC_FOR_G(D, X) \
@@ -769,9 +798,9 @@ hipError_t prefill_occupancy(int D, int G, bool stats, int ks, int *blocks) {
   return hipErrorInvalidValue;
 }
 
-hipError_t launch_prefill(int D, int G, int grid, bool stats, int ks, AttnRows rows, PrefillWs ws, int Hkv,
+hipError_t launch_prefill(int D, int G, int grid, bool stats, int ks, int tile_rows, AttnRows rows, PrefillWs ws, int Hkv,
                           float scale_log2, hipStream_t stream) {
-#define LAUNCH(DD, GG) return launch_prefill_dg<DD, GG>(grid, stats, ks, rows, ws, Hkv, scale_log2, stream)
+#define LAUNCH(DD, GG) return launch_prefill_dg<DD, GG>(grid, stats, ks, tile_rows, rows, ws, Hkv, scale_log2, stream)
   if (D == 64) {
     SONIC_FOR_G(64, LAUNCH)
   } else if (D == 128) {

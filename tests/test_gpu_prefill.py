@@ -239,3 +239,24 @@ def test_prefill_many_runs():
     rows = [np.unique(np.concatenate([rng.integers(0, lay.length, 150), np.arange(lay.length - 50, lay.length)])) for lay in lays]
     for b, want in enumerate(H.oracle_prefill_rows(batch, rows)):
         H.assert_close(got[int(batch.cu_seqlens[b]) + rows[b]], want, f"request {b}")
+
+
+@pytest.mark.parametrize("Hq,Hkv,d", [(2, 2, 128), (4, 2, 128), (3, 3, 64), (2, 1, 64)])
+def test_prefill_row_blocks(Hq, Hkv, d):
+    """One and two q-heads per kv-head: several 32-row blocks share a workgroup.  Runs of every
+    remainder of the blocks, the first rows of a request among them, both variants."""
+    H.need_gpu()
+    lays = [W.RequestLayout(1, [31, 32, 33, 64, 65], [1, 33, 64, 2, 127], 129), W.RequestLayout(130, [128], [97], 96),
+            W.RequestLayout(0, [], [], 63)]
+    batch = W.make_batch("blocks", lays, Hq, Hkv, d, seed=5 + Hq + d)
+    db = H.device_batch(batch)
+    assert db.prefill() == sonic.OK
+    plain = db.out.clone()
+    mass = torch.empty((batch.q.shape[0], Hq), dtype=torch.float32, device="cuda")
+    assert db.prefill(nexus_mass=mass) == sonic.OK
+    torch.cuda.synchronize()
+    assert db.read_status() == 0 and torch.equal(plain, db.out)
+    got = plain.cpu().numpy()
+    rows = [np.arange(lay.length) for lay in lays]
+    for b, want in enumerate(H.oracle_prefill_rows(batch, rows)):
+        H.assert_close(got[int(batch.cu_seqlens[b]) + rows[b]], want, f"request {b}")

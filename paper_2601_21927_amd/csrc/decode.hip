@@ -559,9 +559,12 @@ DecodeShape decode_shape(int batch, int Hkv, int G, int D, int max_ctx, bool mas
   // 33.0), as where the second round of 512 would be at most half full (768 workgroups of
   // 1.5k rows: 118.6, with four 121.8).  D = 64 fits twice with eight (64 pairs of 4k rows
   // 13.0, with four 13.4).
+  // Up to 256 rows a range, four waves also merge and start sooner: 64 pairs of 64 rows 5.1
+  // us with four, 5.5 with eight; 88 pairs of up to 289 rows 8.7 and 8.3.
+  const bool tiny = max_ctx <= 256L * sh.splits;
   const bool two = (slots >= 480 && slots <= 512) || slots > 768;
   const bool brief = slots >= 256 && slots < 480 && max_ctx <= 512L * sh.splits;
-  if (sh.target > 0 || (!masked && D == 128 && (two || brief))) sh.waves = 4;
+  if (sh.target > 0 || (!masked && (tiny || (D == 128 && (two || brief))))) sh.waves = 4;
   return sh;
 }
 

@@ -101,7 +101,8 @@ __device__ __forceinline__ bool local_routes(const uint8_t *__restrict__ role, i
   constexpr int NW = kPThreads / kWave;
   static_assert(kLocalRounds * NW == 2 * kWave, "two counts per lane");
   __shared__ int cnt[2 * kWave];
-  const int32_t pending = __hip_atomic_load(status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __shared__ int s_ok;   // one thread's look at the status word decides for every wave
+  if (threadIdx.x == 0) s_ok = __hip_atomic_load(status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0;
   const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
   uint8_t mine[kLocalRounds];
 #pragma unroll
@@ -109,7 +110,6 @@ __device__ __forceinline__ bool local_routes(const uint8_t *__restrict__ role, i
     mine[j] = kText;
     if (j * kPThreads < T) mine[j] = role[min(j * kPThreads + static_cast<int>(threadIdx.x), T - 1)];
   }
-  if (pending != 0) return false;   // nothing raises the status in this call: the same answer in every wave
 #pragma unroll
   for (int j = 0; j < kLocalRounds; ++j) {
     const bool nx = j * kPThreads + threadIdx.x < T && mine[j] == kNexus;
@@ -119,6 +119,7 @@ __device__ __forceinline__ bool local_routes(const uint8_t *__restrict__ role, i
     if (lane == 0) cnt[j * NW + wave] = __popcll(m);
   }
   __syncthreads();
+  if (!s_ok) return false;
   // every wave scans the 128 counts: lane l holds counts 2l and 2l + 1
   const int c0 = cnt[2 * lane], c1 = cnt[2 * lane + 1];
   int incl = c0 + c1;

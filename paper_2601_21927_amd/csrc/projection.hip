@@ -360,17 +360,24 @@ __global__ __launch_bounds__(NW * kWave) void skinny_proj_kernel(
   constexpr int RS = C + 1;                       // row stride of the partial sums, in floats
   static_assert((S - 1) * IN < 64, "the wait count fits vmcnt");
   static_assert(NW * R * RS * sizeof(float) <= NW * S * SLOT * sizeof(uint16_t), "the partial sums fit in the ring");
-  __shared__ __align__(16) uint16_t ring[NW * S * SLOT];
+  constexpr int RING = NW * S * SLOT;
+  constexpr bool kRoom = RING * sizeof(uint16_t) + 16 <= 160 * 1024;   // ... for the decision behind the ring
+  __shared__ __align__(16) uint16_t ring[RING + (kRoom ? 8 : 0)];
   const bool nexus = blockIdx.y != 0;
   const int n0 = blockIdx.x * C, r0 = blockIdx.z * R;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const int lane = threadIdx.x % kWave;
-  // one round trip for the status word and the roles (every wave for itself: the same answer)
-  const int32_t pending = __hip_atomic_load(status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  // One thread's look at the status word decides for every wave: the word may change
+  // between two looks, and a wave that left alone would leave its partial sums unwritten.
+  // One round trip for it and the roles.
+  int *const s_ok = reinterpret_cast<int *>(ring + (kRoom ? RING : 0));
+  if (threadIdx.x == 0) *s_ok = __hip_atomic_load(status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0;
   static_assert(R <= 2 * kWave, "two roles per lane");
   const bool m0 = (role[min(r0 + min(lane, R - 1), T - 1)] == kNexus) == nexus;   // rows past the end repeat one
   const bool m1 = R > kWave && (role[min(r0 + min(lane + kWave, R - 1), T - 1)] == kNexus) == nexus;
-  if (pending != 0 || !__any(m0 || m1)) return;
+  __syncthreads();
+  if (*s_ok == 0 || !__any(m0 || m1)) return;
+  if (!kRoom) __syncthreads();   // the ring is filled over the word
 
   const int nk = K / kPK;
   const int per = (nk + NW - 1) / NW;

@@ -166,3 +166,29 @@ def test_projection_tile_shapes(T, K, N):
     x, wt, wn = _bits(rng, (T, K)), _bits(rng, (N, K), 0.05), _bits(rng, (N, K), 0.05)
     for role in (np.where(np.arange(T) % 7 < 2, OL.NEXUS, OL.CURRENT).astype(np.uint8), np.full(T, OL.NEXUS, np.uint8)):
         check(run(role, x, wt, wn), role, x, wt, wn, f"T={T} K={K} N={N}")
+
+
+@pytest.mark.parametrize("T,K,N", [(8, 1024, 1000), (40, 640, 4113), (100, 512, 6000), (600, 256, 300)])
+def test_projection_status_changes_while_it_runs(T, K, N):
+    """Another stream raises and clears the status word while calls run: whatever a call's
+    workgroups see, every value of y is either untouched or the one of a call left alone."""
+    rng = np.random.default_rng(T + N)
+    x, wt, wn = _bits(rng, (T, K)), _bits(rng, (N, K), 0.05), _bits(rng, (N, K), 0.05)
+    role = np.where(np.arange(T) % 3 == 0, OL.NEXUS, OL.CURRENT).astype(np.uint8)
+    want = torch.from_numpy(run(role, x, wt, wn)).cuda()
+    r, dx, dt, dn = torch.from_numpy(role).cuda(), bf16_to_device(x), bf16_to_device(wt), bf16_to_device(wn)
+    ws = torch.empty(sonic.role_projection_workspace_bytes(T), dtype=torch.uint8, device="cuda")
+    status = torch.zeros(1, dtype=torch.int32, device="cuda")
+    ys = torch.full((32, T, N), float("nan"), dtype=torch.float32, device="cuda")
+    side = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    for y in ys:
+        with torch.cuda.stream(side):
+            for _ in range(3):
+                status.fill_(sonic.ERR_BAD_LAYOUT)
+                status.zero_()
+        assert sonic.role_projection(r, dx, dt, dn, y, ws, status) == sonic.OK
+    torch.cuda.synchronize()
+    for i, y in enumerate(ys):
+        left = torch.isnan(y)
+        assert bool((left | (y == want)).all()), f"call {i}"

@@ -37,11 +37,8 @@ constexpr int kPThreads = kPWavesM * kPWavesN * kWave;
 
 // Pass 1: Nexus rows per block of 1024 rows.
 __global__ __launch_bounds__(kRouteThreads) void route_count_kernel(const uint8_t *__restrict__ role, int T,
-                                                                    int32_t *__restrict__ blk_nexus,
-                                                                    const int32_t *status) {
+                                                                    int32_t *__restrict__ blk_nexus) {
   __shared__ int lds[kRouteThreads / kWave + 1];
-  __shared__ int s_ok;
-  if (!block_status_clear(status, &s_ok)) return;
   const int i = blockIdx.x * kRouteThreads + threadIdx.x;
   int tot;
   block_flag_scan<kRouteThreads>(i < T && role[i] == kNexus, &tot, lds);
@@ -49,6 +46,8 @@ __global__ __launch_bounds__(kRouteThreads) void route_count_kernel(const uint8_
 }
 
 // Pass 2 (one workgroup): Nexus rows before each block, in place; counts = (non-Nexus, Nexus).
+// Its look at the status word decides for the whole call: the word may change at any time,
+// and a tile must find either no rows or every slot of the permutation filled.
 __global__ __launch_bounds__(kRouteThreads) void route_scan_kernel(int nblk, int T, int32_t *__restrict__ blk_nexus,
                                                                    int32_t *__restrict__ counts,
                                                                    const int32_t *status) {
@@ -58,10 +57,10 @@ __global__ __launch_bounds__(kRouteThreads) void route_scan_kernel(int nblk, int
   int carry = 0;
   for (int base = 0; base < nblk; base += kRouteThreads) {
     const int i = base + threadIdx.x;
-    const int v = (ok && i < nblk) ? blk_nexus[i] : 0;
+    const int v = i < nblk ? blk_nexus[i] : 0;
     int tot;
     const int off = block_int_scan<kRouteThreads>(v, &tot, lds);
-    if (ok && i < nblk) blk_nexus[i] = carry + off;
+    if (i < nblk) blk_nexus[i] = carry + off;
     carry += tot;
   }
   if (threadIdx.x == 0) {   // no rows at all when the status is set: every GEMM tile exits
@@ -70,15 +69,13 @@ __global__ __launch_bounds__(kRouteThreads) void route_scan_kernel(int nblk, int
   }
 }
 
-// Pass 3: row i to its slot of the permutation.
+// Pass 3: row i to its slot of the permutation, unless pass 2 stopped the call.
 __global__ __launch_bounds__(kRouteThreads) void route_fill_kernel(const uint8_t *__restrict__ role, int T,
                                                                    const int32_t *__restrict__ blk_nexus,
                                                                    const int32_t *__restrict__ counts,
-                                                                   int32_t *__restrict__ perm,
-                                                                   const int32_t *status) {
+                                                                   int32_t *__restrict__ perm) {
   __shared__ int lds[kRouteThreads / kWave + 1];
-  __shared__ int s_ok;
-  if (!block_status_clear(status, &s_ok)) return;
+  if (counts[0] + counts[1] != T) return;
   const int i = blockIdx.x * kRouteThreads + threadIdx.x;
   const bool in = i < T;
   const bool nx = in && role[i] == kNexus;
@@ -503,9 +500,9 @@ hipError_t launch_routed_gemm(int T, int K, int N, const uint8_t *role, const ui
   const bool local = T <= kLocalRows;
   if (!local) {
     const int nblk = (T + kRouteThreads - 1) / kRouteThreads;
-    route_count_kernel<<<dim3(nblk), dim3(kRouteThreads), 0, stream>>>(role, T, blk_nexus, status);
+    route_count_kernel<<<dim3(nblk), dim3(kRouteThreads), 0, stream>>>(role, T, blk_nexus);
     route_scan_kernel<<<dim3(1), dim3(kRouteThreads), 0, stream>>>(nblk, T, blk_nexus, counts, status);
-    route_fill_kernel<<<dim3(nblk), dim3(kRouteThreads), 0, stream>>>(role, T, blk_nexus, counts, perm, status);
+    route_fill_kernel<<<dim3(nblk), dim3(kRouteThreads), 0, stream>>>(role, T, blk_nexus, counts, perm);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }

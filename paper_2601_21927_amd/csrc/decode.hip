@@ -42,6 +42,11 @@
 namespace sonic {
 
 constexpr int kGroupRows = 16;
+// In a completion counter: a workgroup that counted found an error on the status word.  The
+// word may change while a call runs, so the workgroups (and waves) of one call may see
+// different values; each counts all the same, which leaves the counters at zero for the
+// next call, and what such a workgroup had a part in is not merged and not advanced.
+constexpr int kStopBit = 1 << 30;
 constexpr int kMaxSplits = 16;   // of a (request, kv-head): the merge loads all its partials in one round trip
 
 typedef short v4i16 __attribute__((ext_vector_type(4)));
@@ -75,6 +80,11 @@ template <int N> __device__ __forceinline__ float row_rotate(float x) {
   return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x120 | N, 0xF, 0xF, false));
 }
 
+__device__ __forceinline__ bool stops(int32_t pending) {
+  pending = __builtin_amdgcn_readfirstlane(pending);
+  return pending != 0 && pending != SONIC_ERR_CAPACITY;
+}
+
 template <int D, int G, bool MASKED, int NW, bool BAL>
 __global__ __launch_bounds__(NW * kWave, 2) void decode_kernel(
     uint16_t *__restrict__ kc, uint16_t *__restrict__ vc, const int64_t *__restrict__ row_off,
@@ -106,6 +116,7 @@ __global__ __launch_bounds__(NW * kWave, 2) void decode_kernel(
   __shared__ float m_lds[NW][16];
   __shared__ float l_lds[NW][16];
   __shared__ int s_last;
+  __shared__ int s_stop[NW];   // each wave's look at the status word
   static_assert(sizeof(float) * NW * G * DP <= sizeof(uint16_t) * NW * 4 * SLOT,
                 "the merge fits in the ring");
 
@@ -116,6 +127,10 @@ __global__ __launch_bounds__(NW * kWave, 2) void decode_kernel(
   const int nsplit = gridDim.x;   // BAL: workgroups of a kv-head
   int split, b, nsp, R, len;
   int64_t base;
+  // A pending error other than a capacity error (a layout error of an earlier call) stops
+  // the whole call: nothing is appended, written or advanced.  A wave that sees one loads
+  // no rows and goes on to the workgroup's count (see kStopBit).
+  bool stop;
   // BAL: the workgroup's plan.  Lane l looks at request l (at most 64): its length,
   // capacity and first row, all requested together with the status word.  A split is R
   // rows, the same for every request: the batch's rows over the kv-head's `target`
@@ -128,8 +143,8 @@ __global__ __launch_bounds__(NW * kWave, 2) void decode_kernel(
     const int32_t pending = __hip_atomic_load(status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     const int ll = cache_len[lb], lc = row_cap[lb];
     const int64_t lo = row_off[lb];
-    if (pending != 0 && pending != SONIC_ERR_CAPACITY) return;
-    const bool fits = ll + 1 <= lc && ll + 1 <= max_ctx;
+    stop = stops(pending);
+    const bool fits = ll >= 0 && ll < lc && ll < max_ctx;   // (behind an error a length may be anything)
     if (__any(!fits) && blockIdx.x == 0 && kvh == 0 && threadIdx.x == 0) raise_status(status, SONIC_ERR_CAPACITY);
     lane_ctx = l < batch && fits ? ll + 1 : 0;
     const int groups = (lane_ctx + kGroupRows - 1) / kGroupRows;
@@ -166,13 +181,10 @@ __global__ __launch_bounds__(NW * kWave, 2) void decode_kernel(
     len = cache_len[b];
     const int cap = row_cap[b];
     base = row_off[b];
-    asm volatile("" ::"s"(base));
-    // A pending error other than a capacity error (a layout error of an earlier call)
-    // stops the whole call: nothing is appended, written or advanced.  Only capacity
-    // errors can appear during the call (raised below, per request), so every
-    // workgroup of the call takes the same decision and no counter is touched.
-    if (pending != 0 && pending != SONIC_ERR_CAPACITY) return;
-    if (len + 1 > cap || len + 1 > max_ctx) {   // uniform over the request: no append, no output
+    asm volatile("" ::"s"(len), "s"(cap), "s"(base));
+    __builtin_amdgcn_sched_barrier(0);   // none of the three is looked at before all are requested
+    stop = stops(pending);
+    if (len < 0 || len >= cap || len >= max_ctx) {   // uniform over the request: no append, no output, no count
       if (split == 0 && kvh == 0 && threadIdx.x == 0) raise_status(status, SONIC_ERR_CAPACITY);
       return;
     }
@@ -191,27 +203,53 @@ __global__ __launch_bounds__(NW * kWave, 2) void decode_kernel(
   // the last of the call advances every length.  A workgroup has read the lengths before
   // it counts, so none can still see an advanced one.
   const int all = BAL ? Hkv * (__popcll(__ballot(lane_ctx > 0)) + nsplit - used) : Hkv;
-  auto count = [&]() {
-    return __hip_atomic_fetch_add(&ws.done[BAL ? 0 : b], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  auto add_one = [&](int32_t *counter, bool stopped) {
+    if (stopped) __hip_atomic_fetch_or(counter, kStopBit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return __hip_atomic_fetch_add(counter, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   };
+  auto count = [&](bool stopped) { return add_one(&ws.done[BAL ? 0 : b], stopped); };
   auto advance = [&](int old) {   // the first wave; `old` is its first lane's
-    if (__builtin_amdgcn_readfirstlane(old) != all - 1) return;
-    if (BAL) {
-      if (lane_ctx > 0) cache_len[threadIdx.x] = lane_ctx;
-    } else if (threadIdx.x == 0) {
-      cache_len[b] = n_ctx;
+    old = __builtin_amdgcn_readfirstlane(old);
+    if ((old & ~kStopBit) != all - 1) return;
+    if ((old & kStopBit) == 0) {
+      if (BAL) {
+        if (lane_ctx > 0) cache_len[threadIdx.x] = lane_ctx;
+      } else if (threadIdx.x == 0) {
+        cache_len[b] = n_ctx;
+      }
     }
     if (threadIdx.x == 0) ws.done[BAL ? 0 : b] = 0;
+  };
+  if (lane == 0) s_stop[wave] = stop;
+  auto any_stop = [&]() {   // behind a barrier
+    int any = 0;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) any |= s_stop[w];
+    return __builtin_amdgcn_readfirstlane(any) != 0;
   };
 
   // Every split counts itself once, after its partial (if any) is stored.  The last
   // to count merges the partials of the nsp splits with rows by log-sum-exp, all of them
   // in one memory round trip, writes the output, and counts the pair for its request
   // while the partials load; the last pair of a request advances the length.
-  auto finish_pair = [&]() {
-    if (threadIdx.x == 0) s_last = (atomicAdd(&ws.arrive[pair], 1) == (BAL ? nsp : nsplit) - 1);
+  auto finish_pair = [&](bool stopped) {
+    if (threadIdx.x == 0) {
+      const int old = add_one(&ws.arrive[pair], stopped);
+      s_last = (old & ~kStopBit) == (BAL ? nsp : nsplit) - 1 ? ((old & kStopBit) != 0 ? 2 : 1) : 0;
+    }
     __syncthreads();
     if (!s_last) return;
+    if (__builtin_expect(s_last == 2, 0)) {   // a split of the pair was stopped: nothing to merge
+      if (threadIdx.x < kWave) {
+        int old_done = 0;
+        if (threadIdx.x == 0) {
+          ws.arrive[pair] = 0;
+          old_done = count(true);
+        }
+        advance(old_done);
+      }
+      return;
+    }
     // Thread u merges values 4u .. 4u + 3 (of q-head u / (D / 4)).  For the weights, lane
     // 16 j + i of a wave takes split i of the wave's j-th q-head.
     static_assert(G * D / 4 <= NW * kWave && kMaxSplits == 16, "one pass; a row of lanes holds a head's splits");
@@ -233,7 +271,7 @@ __global__ __launch_bounds__(NW * kWave, 2) void decode_kernel(
     // behind the loads, so that the round trips pass together (the compiler waits for an
     // atomic's result on the spot)
     int old_done = 0;
-    if (threadIdx.x == 0) old_done = count();
+    if (threadIdx.x == 0) old_done = count(false);
     const float m = sp < nsp ? __uint_as_float(ml[0]) : -INFINITY;
     float top = m;
     top = fmaxf(top, row_rotate<8>(top));
@@ -265,11 +303,12 @@ __global__ __launch_bounds__(NW * kWave, 2) void decode_kernel(
   };
   if (split >= nsp) {   // no rows (only when nsplit > 1)
     __syncthreads();    // every wave has read the lengths: the workgroup may count
+    const bool stopped = any_stop();
     if (!BAL) {
-      finish_pair();
+      finish_pair(stopped);
     } else if (threadIdx.x < kWave) {
       int old = 0;
-      if (threadIdx.x == 0) old = count();
+      if (threadIdx.x == 0) old = count(stopped);
       advance(old);
     }
     return;
@@ -277,7 +316,7 @@ __global__ __launch_bounds__(NW * kWave, 2) void decode_kernel(
   const bool whole = BAL ? nsp == 1 : nsplit == 1;   // the split is all of the pair's context
   const int r_begin = split * R;
   const int r_end = min(n_ctx, r_begin + R);
-  const int ngroups = (r_end - r_begin + kGroupRows - 1) / kGroupRows;
+  const int ngroups = stop ? 0 : (r_end - r_begin + kGroupRows - 1) / kGroupRows;
   const int col = lane & 15;       // score column (q-head) / value-product column
   const int quarter = lane >> 4;   // score rows 4*quarter .. +3
   const size_t row_stride = static_cast<size_t>(Hkv) * D;
@@ -291,7 +330,7 @@ __global__ __launch_bounds__(NW * kWave, 2) void decode_kernel(
   // own before the pipeline starts); the stores happen after the streaming.  Rows of
   // this call read the new token from k_new / v_new, so nothing here depends on them.
   const bool appender = split == 0 && wave == 0;
-  if (appender) {
+  if (appender && !stop) {
     const int c = lane < 2 * DC ? lane % DC : 0;
     dma16((lane >= DC && lane < 2 * DC ? vnew : knew) + c * 8, app_lds);
   }
@@ -300,7 +339,7 @@ __global__ __launch_bounds__(NW * kWave, 2) void decode_kernel(
   // Q^T fragments (B operand of the scores) are read from there once the first wait
   // has passed: lane (col, quarter) takes d = 32*ks + 8*quarter .. +7 of q-head
   // kvh*G + col (columns col >= G take head kvh*G and are never read back).
-  {
+  if (!stop) {
     const uint16_t *q0 = q + (static_cast<size_t>(b) * Hq + kvh * G) * D;
 #pragma unroll
     for (int i = 0; i < NQ; ++i) {
@@ -432,8 +471,10 @@ __global__ __launch_bounds__(NW * kWave, 2) void decode_kernel(
 
   // two-deep pipeline: a slot is refilled as soon as its group has been processed
   int ga = wave, gb = wave + NW;   // the groups in ring slots 0 and 1
-  issue(ga, 0);
-  issue(gb, 1);
+  if (!stop) {
+    issue(ga, 0);
+    issue(gb, 1);
+  }
   wait_vm<NG>();                          // Q and slot 0 have landed (slot 1 may not have)
   read_q();
   while (ga < ngroups) {
@@ -448,7 +489,7 @@ __global__ __launch_bounds__(NW * kWave, 2) void decode_kernel(
     wait_vm<NG>();
   }
   wait_vm<0>();   // the trailing (unused) loads, before the ring is reused
-  if (appender && lane < 2 * DC) {
+  if (appender && !stop && lane < 2 * DC) {
     const size_t dst = static_cast<size_t>(len) * row_stride + (lane % DC) * 8;
     *reinterpret_cast<u32x4 *>((lane < DC ? kbase : vbase) + dst) = *reinterpret_cast<const u32x4 *>(&app_lds[lane * 8]);
   }
@@ -460,6 +501,7 @@ __global__ __launch_bounds__(NW * kWave, 2) void decode_kernel(
     l_lds[wave][col] = l_run;
   }
   __syncthreads();   // every wave is done with the ring
+  const bool stopped = any_stop();
   // [wave][G][DP]: a lane's four values are consecutive d, written at once; with rows of D
   // floats the G heads of a column block all met in one bank
   float *acc_lds = reinterpret_cast<float *>(ring);
@@ -485,6 +527,7 @@ __global__ __launch_bounds__(NW * kWave, 2) void decode_kernel(
 #pragma unroll
       for (int e = 0; e < 4; ++e) A[e] = fmaf(sc, a[e], A[e]);
     }
+    if (stopped) break;
     if (whole) {
       *reinterpret_cast<f32x4 *>(orow + 4 * u) = f32x4{A[0] / L, A[1] / L, A[2] / L, A[3] / L};
     } else {   // write-through at system scope (see the top of the file)
@@ -499,10 +542,10 @@ __global__ __launch_bounds__(NW * kWave, 2) void decode_kernel(
   if (!whole) {
     wait_vm<0>();      // this thread's partial is stored
     __syncthreads();   // ... and every thread's
-    finish_pair();
+    finish_pair(stopped);
   } else if (threadIdx.x < kWave) {
     int old = 0;
-    if (threadIdx.x == 0) old = count();
+    if (threadIdx.x == 0) old = count(stopped);
     advance(old);
   }
 }

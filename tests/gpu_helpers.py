@@ -113,3 +113,22 @@ def oracle_compact(batch: W.Batch, caps, fill=0xFFFF):
 
 def kept_counts(batch: W.Batch):
     return np.array([lay.system + sum(lay.nexus) + lay.current for lay in batch.layouts], np.int64)
+
+
+class Flips:
+    """A second stream that raises and clears a status word many times: start() lets it run,
+    so that what the caller enqueues next on its own stream runs meanwhile."""
+
+    def __init__(self, status, code, times=300):
+        self.stream = torch.cuda.Stream()
+        self.stream.wait_stream(torch.cuda.current_stream())
+        self.graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(self.graph, stream=self.stream):
+            for _ in range(times):
+                status.fill_(code)
+                status.fill_(0)
+        torch.cuda.synchronize()
+
+    def start(self):
+        with torch.cuda.stream(self.stream):
+            self.graph.replay()

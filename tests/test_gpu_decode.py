@@ -281,3 +281,52 @@ def test_decode_work_split(B, Hq, Hkv, d, lens, max_ctx):
             assert np.array_equal(gk[o:o + n + 1], k[o:o + n + 1]) and np.array_equal(gv[o:o + n + 1], v[o:o + n + 1])
             lens[b] += 1
         assert np.array_equal(cache.length.cpu().numpy(), lens)
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,d,lens,max_ctx", [
+    (64, 16, 4, 128, (5, 300, 700), 2048),       # rows shared over the batch
+    (8, 32, 8, 128, (900, 37), 1000),            # four splits per pair
+    (64, 28, 4, 128, (5, 60, 200), 256)])        # one split per pair
+def test_decode_status_changes_while_it_runs(B, Hq, Hkv, d, lens, max_ctx):
+    """Another stream raises and clears a layout error while calls run: a pair's output is
+    untouched or the one of a call left alone, a length is advanced or not, and the counters
+    in the workspace are at zero again, so that the next call is right."""
+    H.need_gpu()
+    rng = np.random.default_rng(B + Hq)
+    lens = np.array([lens[b % len(lens)] for b in range(B)], np.int64)
+    cache, _, _ = plain_caches(rng, lens, 2, Hkv, d)
+    q, kn, vn = (bf16_to_device(W.f32_to_bf16_bits(rng.standard_normal((B, h, d)).astype(np.float32)))
+                 for h in (Hq, Hkv, Hkv))
+    len0 = torch.from_numpy(lens.astype(np.int32)).cuda()
+    status = torch.zeros(1, dtype=torch.int32, device="cuda")
+    ws = torch.zeros(sonic.decode_workspace_bytes(B, Hq, d, max_ctx), dtype=torch.uint8, device="cuda")
+    counters = ws[:(4 * B + 255) // 256 * 256 + 4 * B * Hkv]
+
+    def call(out):
+        cache.length.copy_(len0)
+        assert sonic.compressed_decode(cache.k, cache.v, cache.row_off, cache.row_cap, cache.length, q, kn, vn, out,
+                                       ws, status, max_ctx) == sonic.OK
+    want = torch.empty((B, Hq, d), dtype=torch.float32, device="cuda")
+    call(want)
+    outs = torch.full((32, B, Hq, d), float("nan"), dtype=torch.float32, device="cuda")
+    got_len = torch.empty((32, B), dtype=torch.int32, device="cuda")
+    flips = H.Flips(status, sonic.ERR_BAD_LAYOUT)
+    for i, (out, gl) in enumerate(zip(outs, got_len)):
+        if i % 8 == 0:
+            flips.start()
+        call(out)
+        gl.copy_(cache.length)
+    torch.cuda.synchronize()
+    assert not bool(counters.any())
+    left = torch.isnan(outs)
+    assert bool((left | (outs == want)).all())
+    per_pair = left.view(32, B, Hkv, -1)
+    assert bool((per_pair.all(-1) | ~per_pair.any(-1)).all())
+    assert bool(((got_len == len0) | (got_len == len0 + 1)).all())
+    # a request whose length was advanced has all its outputs
+    assert not bool((left.view(32, B, -1).any(-1) & (got_len == len0 + 1)).any())
+    H.note(f"  outputs left out: {float(left.float().mean()):.2f}")
+    again = torch.full_like(want, float("nan"))
+    call(again)
+    torch.cuda.synchronize()
+    assert torch.equal(again, want) and bool((cache.length == len0 + 1).all())

@@ -181,15 +181,13 @@ def test_projection_status_changes_while_it_runs(T, K, N):
     ws = torch.empty(sonic.role_projection_workspace_bytes(T), dtype=torch.uint8, device="cuda")
     status = torch.zeros(1, dtype=torch.int32, device="cuda")
     ys = torch.full((32, T, N), float("nan"), dtype=torch.float32, device="cuda")
-    side = torch.cuda.Stream()
-    torch.cuda.synchronize()
-    for y in ys:
-        with torch.cuda.stream(side):
-            for _ in range(3):
-                status.fill_(sonic.ERR_BAD_LAYOUT)
-                status.zero_()
+    flips = H.Flips(status, sonic.ERR_BAD_LAYOUT)
+    for i, y in enumerate(ys):
+        if i % 8 == 0:
+            flips.start()
         assert sonic.role_projection(r, dx, dt, dn, y, ws, status) == sonic.OK
     torch.cuda.synchronize()
+    H.note(f"  values left out: {float(torch.isnan(ys).float().mean()):.2f}")
     for i, y in enumerate(ys):
         left = torch.isnan(y)
         assert bool((left | (y == want)).all()), f"call {i}"

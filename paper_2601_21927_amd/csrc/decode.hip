@@ -228,6 +228,31 @@ __global__ __launch_bounds__(NW * kWave, 2) void decode_kernel(
     return __builtin_amdgcn_readfirstlane(any) != 0;
   };
 
+  // Behind the store of outputs 4u .. 4u + 3 of the pair (o, normalised by L).  An infinite V
+  // comes out of the sums as NaN (a probability's second part is zero or negative for half of
+  // the rows, a row past a range's end is a copy of its first one times zero, and so is a
+  // split past the last one): where the scores were numbers, the V column is read again, and
+  // one whose only values that are none are infinities of one sign gives that infinity.
+  auto settle_infinities = [&](int u, f32x4 o, float L) {
+    const float all_of = (o[0] + o[1]) + (o[2] + o[3]);
+    if (__builtin_expect(__any(all_of != all_of && L == L), 0)) {
+      const int dd = 4 * (u % (D / 4));
+      const uint16_t *col = vc + (static_cast<size_t>(base) * Hkv + kvh) * D + dd;
+      const uint16_t *last = v_new + static_cast<size_t>(pair) * D + dd;
+      int found[4] = {0, 0, 0, 0};   // 1: +inf, 2: -inf, 4: NaN
+#pragma unroll 4
+      for (int r = 0; r < n_ctx; ++r) {
+        if (MASKED && r < len && row_role[base + r] == kText) continue;
+        const uint16_t *x = r < len ? col + static_cast<size_t>(r) * Hkv * D : last;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) found[e] |= x[e] == 0x7F80 ? 1 : x[e] == 0xFF80 ? 2 : (x[e] & 0x7FFF) > 0x7F80 ? 4 : 0;
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (o[e] != o[e] && L == L && (found[e] == 1 || found[e] == 2)) orow[4 * u + e] = found[e] == 1 ? INFINITY : -INFINITY;
+    }
+  };
+
   // Every split counts itself once, after its partial (if any) is stored.  The last
   // to count merges the partials of the nsp splits with rows by log-sum-exp, all of them
   // in one memory round trip, writes the output, and counts the pair for its request
@@ -297,9 +322,11 @@ __global__ __launch_bounds__(NW * kWave, 2) void decode_kernel(
     if (nsp <= 4) fold(std::integral_constant<int, 4>{});
     else fold(std::integral_constant<int, kMaxSplits>{});
     const float L = __shfl(sum, from);
-    if (threadIdx.x < G * D / 4) *reinterpret_cast<f32x4 *>(orow + 4 * u) = f32x4{A[0] / L, A[1] / L, A[2] / L, A[3] / L};
+    const f32x4 o = {A[0] / L, A[1] / L, A[2] / L, A[3] / L};
+    if (threadIdx.x < G * D / 4) *reinterpret_cast<f32x4 *>(orow + 4 * u) = o;
     if (threadIdx.x == 0) ws.arrive[pair] = 0;
     if (threadIdx.x < kWave) advance(old_done);
+    settle_infinities(u, o, L);
   };
   if (split >= nsp) {   // no rows (only when nsplit > 1)
     __syncthreads();    // every wave has read the lengths: the workgroup may count
@@ -529,7 +556,9 @@ __global__ __launch_bounds__(NW * kWave, 2) void decode_kernel(
     }
     if (stopped) break;
     if (whole) {
-      *reinterpret_cast<f32x4 *>(orow + 4 * u) = f32x4{A[0] / L, A[1] / L, A[2] / L, A[3] / L};
+      const f32x4 o = {A[0] / L, A[1] / L, A[2] / L, A[3] / L};
+      *reinterpret_cast<f32x4 *>(orow + 4 * u) = o;
+      settle_infinities(u, o, L);
     } else {   // write-through at system scope (see the top of the file)
       __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, A), partial_rsrc(acc_rec), u * 16, split * (G * D * 4),
                                              kSystemScope);

@@ -330,3 +330,48 @@ def test_decode_status_changes_while_it_runs(B, Hq, Hkv, d, lens, max_ctx):
     call(again)
     torch.cuda.synchronize()
     assert torch.equal(again, want) and bool((cache.length == len0 + 1).all())
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,d,lens,max_ctx", [
+    (64, 8, 4, 128, (3, 300, 700), 2048),     # rows shared over the batch
+    (8, 32, 8, 128, (900, 37, 640), 1000),    # four splits per pair
+    (64, 28, 4, 128, (5, 60, 200), 256),      # one split per pair, four waves
+    (3, 8, 8, 64, (100, 33, 900), 1000)])     # several splits, eight waves
+def test_decode_infinite_values(B, Hq, Hkv, d, lens, max_ctx):
+    """One V row per column of d is infinite (the first row of every 16-row group among
+    them, so also the one that stands in for the rows past a range's end): that column of the
+    output is that infinity, every other one is what the oracle says."""
+    H.need_gpu()
+    rng = np.random.default_rng(B + d)
+    lens = np.array([lens[b % len(lens)] for b in range(B)], np.int64)
+    cache, k, v = plain_caches(rng, lens, 2, Hkv, d)
+    off = cache.row_off_host
+    rows = [np.unique(np.concatenate([np.arange(0, n, 16), [n // 2, n - 1]]))[:d - 8] for n in lens]
+    signs = np.where(np.arange(d) % 3 == 0, 0xFF80, 0x7F80).astype(np.uint16)
+    finite = v.copy()
+    for b, rs in enumerate(rows):
+        for j, r in enumerate(rs):
+            v[off[b] + r, :, j] = signs[j]
+    cache.v.copy_(bf16_to_device(v))
+    status = torch.zeros(1, dtype=torch.int32, device="cuda")
+    out = torch.empty((B, Hq, d), dtype=torch.float32, device="cuda")
+    q, kn, vn = (W.f32_to_bf16_bits(rng.standard_normal((B, h, d)).astype(np.float32)) for h in (Hq, Hkv, Hkv))
+    fin_new = vn.copy()
+    vn[:, :, d - 1] = 0x7F80
+    assert cache.decode(bf16_to_device(q), bf16_to_device(kn), bf16_to_device(vn), out, status, max_ctx) == sonic.OK
+    torch.cuda.synchronize()
+    assert int(status.item()) == 0
+    got = out.cpu().numpy()
+    for b in range(B):
+        o, n = int(off[b]), int(lens[b])
+        if b >= 6 and b != B - 1:
+            continue
+        want = OD.decode_step(q[b], k[o:o + n], finite[o:o + n], kn[b], fin_new[b])
+        m = len(rows[b])
+        inf = np.where(signs == 0x7F80, np.inf, -np.inf)
+        want[:, :m] = inf[:m]
+        want[:, d - 1] = np.inf
+        assert np.array_equal(np.isfinite(got[b]), np.isfinite(want)), f"request {b}"
+        ok = np.isfinite(want)
+        assert np.array_equal(got[b][~ok], want[~ok]), f"request {b}"
+        assert np.abs(got[b][ok] - want[ok]).max() <= 1e-4, f"request {b}"   # as in test_decode_work_split

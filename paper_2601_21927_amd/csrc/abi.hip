@@ -44,7 +44,6 @@ hipError_t launch_compact(int batch, int total_tokens, int max_seqlen, int Hkv, 
                           const uint16_t *k, const uint16_t *v, uint16_t *kc, uint16_t *vc, const int64_t *row_off,
                           const int32_t *row_cap, int32_t *cache_len, int32_t *keep_idx, int32_t *status,
                           hipStream_t stream);
-int decode_splits(int batch, int Hkv, int max_ctx);
 DecodeShape decode_shape(int batch, int Hkv, int G, int D, int max_ctx, bool masked, size_t part_bytes);
 size_t decode_ws_layout(int batch, int Hkv, size_t part_bytes, DecodeWs *ws, char *base);
 size_t decode_scratch_layout(int batch, int Hkv, size_t part_bytes, DecodeWs *ws, char *base);
@@ -569,8 +568,6 @@ size_t sonic_decode_workspace_bytes(int32_t batch, int32_t Hq, int32_t d, int32_
   size_t part = 0;
   for (int hkv = 1; hkv <= Hq; ++hkv) {
     if (Hq % hkv != 0 || Hq / hkv > 8) continue;
-    const int nsplit = decode_splits(batch, hkv, max_ctx);
-    if (nsplit > 1) part = std::max(part, static_cast<size_t>(batch) * Hq * nsplit * (d + 2) * sizeof(float));
     part = std::max(part, decode_shape(batch, hkv, Hq / hkv, d, max_ctx, false, SIZE_MAX).part_bytes);
   }
   return align_up(decode_counter_bytes(batch, Hq) + part, 256);

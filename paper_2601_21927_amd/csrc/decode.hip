@@ -37,6 +37,7 @@
 #include "common.h"
 #include "scan.h"
 
+#include <algorithm>
 #include <type_traits>
 
 namespace sonic {
@@ -589,7 +590,7 @@ __global__ __launch_bounds__(NW * kWave, 2) void decode_kernel(
 // or more, one split, or three when the longest context reaches 2048 rows, so that
 // the longest pairs do not outlast the rest of the call when lengths are uneven
 // (dynamic-budget batch: 1 split 127.7 us, 2 117.1, 3 111.4, 4 121.3 per call).
-int decode_splits(int batch, int Hkv, int max_ctx) {
+static int decode_splits(int batch, int Hkv, int max_ctx) {
   const long pairs = static_cast<long>(batch) * Hkv;
   if (pairs >= 256) return max_ctx >= 2048 ? 3 : 1;
   long s = 256 / pairs;
@@ -604,6 +605,8 @@ DecodeShape decode_shape(int batch, int Hkv, int G, int D, int max_ctx, bool mas
   DecodeShape sh{decode_splits(batch, Hkv, max_ctx), 0, 8, 0};
   const long pairs = static_cast<long>(batch) * Hkv;
   auto part = [&](long slots) { return static_cast<size_t>(slots) * G * (D + 2) * sizeof(float); };
+  // what a call needs, however it is cut: a smaller workspace is refused
+  const size_t least = sh.splits > 1 ? part(pairs * sh.splits) : 0;
   // Evenly shared rows (see the kernel) where a call fills the GPU several times over and
   // contexts may be long and uneven.  512 four-wave workgroups are resident; a request's
   // last split is half empty on average, so `target` aims at whole rounds of 512 with
@@ -615,13 +618,13 @@ DecodeShape decode_shape(int batch, int Hkv, int G, int D, int max_ctx, bool mas
     long rounds = 2;
     while (512 * rounds - pairs / 2 < pairs) ++rounds;
     const long target = (512 * rounds - pairs / 2 + Hkv - 1) / Hkv;
-    if (part((target + batch) * Hkv) <= part_bytes) {
+    if (std::max(least, part((target + batch) * Hkv)) <= part_bytes) {
       sh.target = static_cast<int>(target);
       sh.splits = static_cast<int>(target + batch);
     }
   }
   const long slots = sh.target > 0 ? static_cast<long>(sh.splits) * Hkv : pairs * sh.splits;
-  sh.part_bytes = sh.splits > 1 ? part(slots) : 0;
+  sh.part_bytes = std::max(least, sh.target > 0 ? part(slots) : 0);
   // Four waves, two workgroups per CU, where there are enough workgroups: one starts and
   // merges while the other streams (512 pairs of 200 rows 13.7 us with four, 18.1 with
   // eight), and with one workgroup per CU and short ranges, where starting and merging

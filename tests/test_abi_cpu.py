@@ -162,3 +162,27 @@ def test_softmax_scale_argument_checks_without_gpu():
         assert call(float("nan")) == sonic.ERR_INVALID_ARG
         assert call(float("inf")) == sonic.ERR_INVALID_ARG
     assert st.value == 0
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,d,max_ctx", [(64, 32, 8, 128, 4096), (64, 8, 4, 64, 2048), (37, 56, 7, 64, 8192),
+                                                (32, 32, 32, 128, 4096), (8, 32, 8, 128, 1024)])
+def test_decode_refuses_a_workspace_without_room_for_every_split(B, Hq, Hkv, d, max_ctx):
+    """counters + batch * heads * splits * (d + 2) floats are needed, however the call is cut."""
+    pairs = B * Hkv
+    splits = (3 if max_ctx >= 2048 else 1) if pairs >= 256 else max(1, min(256 // pairs, -(-max_ctx // 256), 16))
+    counters = -(-B * 4 // 256) * 256 + -(-B * Hq * 4 // 256) * 256
+    need = counters + (B * Hq * splits * (d + 2) * 4 if splits > 1 else 0)
+    assert sonic.decode_workspace_bytes(B, Hq, d, max_ctx) >= need
+    p = ctypes.c_void_p(4096)
+    call = lambda n: sonic.lib().sonic_compressed_decode(B, Hq, Hkv, d, max_ctx, p, p, p, p, p, None, p, p, p, 0.0, p, p,
+                                                         n, p, None)
+    assert call(need - 4) == sonic.ERR_WORKSPACE
+    assert call(counters // 2) == sonic.ERR_WORKSPACE
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,d,max_ctx", [(48, 128, 16, 128, 4096), (64, 128, 16, 128, 2048),
+                                                (4097, 4, 1, 64, 64), (1024, 16, 16, 64, 64)])
+def test_decode_without_allocation_refuses_what_its_array_cannot_hold(B, Hq, Hkv, d, max_ctx):
+    p = ctypes.c_void_p(4096)
+    assert sonic.lib().sonic_compressed_decode_noalloc(B, Hq, Hkv, d, max_ctx, p, p, p, p, p, None, p, p, p, 0.0, p, p,
+                                                       None) == sonic.ERR_WORKSPACE

@@ -310,10 +310,11 @@ size_t sonic_decode_workspace_bytes(int32_t batch, int32_t num_q_heads, int32_t 
  * cache_len[b] is incremented on the device, so a decode loop needs no host
  * round trip.  One kernel: the context of each (request, kv-head) is split over
  * up to min(16, 256 / (B * Hkv)) workgroups, and the split that finishes last
- * merges the partials by log-sum-exp.  For 256 or more pairs with max_ctx of 2048
- * and more, up to 64 requests share about 1024 workgroups in proportion to their
- * lengths (at most 16 each); more requests, or a workspace without room for those
- * partials, take three workgroups per pair.
+ * merges the partials by log-sum-exp.  256 to 1023 pairs of up to 64 requests with
+ * max_ctx of 2048 and more and no row_role share 1024 and more workgroups in
+ * proportion to the requests' lengths (at most 16 each); where that does not apply,
+ * or the workspace has no room for those partials, 256 or more pairs take one
+ * workgroup each, or three from max_ctx 2048 on.
  *
  * With row_role == NULL the cache is a compact one and every row is visible.
  * With row_role != NULL (device uint8 [rows], indexed like cache rows) the
@@ -354,8 +355,10 @@ int32_t sonic_compressed_decode(int32_t batch, int32_t num_q_heads, int32_t num_
  * Arguments, outputs and errors are those of sonic_compressed_decode, plus:
  *   - SONIC_ERR_WORKSPACE (returned, nothing enqueued) when the call needs more than
  *     the array holds: batch > 4096, batch * num_kv_heads > 12288, or more than
- *     8 MiB - 64 KiB of partials (batch * num_q_heads * splits * (head_dim + 2) * 4 B,
- *     splits as sonic_decode_workspace_bytes counts them);
+ *     8 MiB - 64 KiB of partials (batch * num_q_heads * splits * (head_dim + 2) * 4 B
+ *     for more than one split, splits being min(16, 256 / pairs, max_ctx / 256 rounded
+ *     up) for fewer than 256 pairs (batch * num_kv_heads), else 1, or 3 from max_ctx
+ *     2048 on);
  *   - calls on one GPU share the array, so calls that overlap on it (concurrent
  *     streams, other threads) race; calls ordered on one stream do not.
  */

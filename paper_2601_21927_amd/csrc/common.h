@@ -207,15 +207,15 @@ struct PrefillWs {
 
 // Device workspace of the decode; the counters are zero between calls.
 struct DecodeWs {
-  int32_t *done;      // [B]      kv-heads of request b finished in this call (balanced: [0] counts the call's)
+  int32_t *done;      // [B]      kv-heads of request b finished in this call (shared rows: and, in the upper bits of [0], requests)
   int32_t *arrive;    // [B*Hkv]  splits of a (request, kv-head) finished in this call
   float *part;        // partials: acc[G][D] of every split, then (max, sum)[G] of every split
 };
 
 // How a decode call is cut into workgroups.
 struct DecodeShape {
-  int splits;         // workgroups per (request, kv-head); balanced: per kv-head
-  int target;         // balanced: workgroups per kv-head that share the rows evenly; otherwise 0
+  int splits;         // workgroups per (request, kv-head); shared rows: per kv-head
+  int target;         // shared rows: of these, the ones to share the rows of the batch; otherwise 0
   int waves;          // waves per workgroup
   size_t part_bytes;  // partials
 };

@@ -33,7 +33,7 @@
 // among the workgroups instead of each request's among its own.  Every workgroup
 // works the shares out from all lengths, so no length may advance while another
 // workgroup has yet to read it: pairs (and workgroups left without rows) count for
-// the whole call, and the last one advances every length.
+// their request, requests for the call, and the last one advances every length.
 #include "common.h"
 #include "scan.h"
 
@@ -48,6 +48,12 @@ constexpr int kGroupRows = 16;
 // different values; each counts all the same, which leaves the counters at zero for the
 // next call, and what such a workgroup had a part in is not merged and not advanced.
 constexpr int kStopBit = 1 << 30;
+// Shared rows, bytes of a cache row (all kv-heads) from which the workgroups of the kv-heads
+// alternate.  With all those of one head before the next, the resident ones read a part of
+// each row, and of long rows that is a part of the memory channels: 16 / 16 heads of 128, 32
+// contexts of 3,000 .. 8,000 rows, 326 us so and 264 alternating.  Shorter rows are better
+// off with a head at a time (32 / 8, 64 contexts of 100 .. 4,000, 52.6 and 55.5).
+constexpr int kLongRow = 4096;
 constexpr int kMaxSplits = 16;   // of a (request, kv-head): the merge loads all its partials in one round trip
 
 typedef short v4i16 __attribute__((ext_vector_type(4)));
@@ -121,11 +127,13 @@ __global__ __launch_bounds__(NW * kWave, 2) void decode_kernel(
   static_assert(sizeof(float) * NW * G * DP <= sizeof(uint16_t) * NW * 4 * SLOT,
                 "the merge fits in the ring");
 
-  const int kvh = blockIdx.y;
+  // BAL: blockIdx.z == 0, the grid is (workgroups, kv-heads) or, with long rows, (kv-heads, workgroups)
+  const bool heads_first = BAL && Hkv * D * 2 >= kLongRow;
+  const int kvh = heads_first ? blockIdx.x : blockIdx.y;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const int lane = threadIdx.x % kWave;
   const int Hq = Hkv * G;
-  const int nsplit = gridDim.x;   // BAL: workgroups of a kv-head
+  const int nsplit = heads_first ? gridDim.y : gridDim.x;   // BAL: workgroups of a kv-head
   int split, b, nsp, R, len;
   int64_t base;
   // A pending error other than a capacity error (a layout error of an earlier call) stops
@@ -134,11 +142,14 @@ __global__ __launch_bounds__(NW * kWave, 2) void decode_kernel(
   bool stop;
   // BAL: the workgroup's plan.  Lane l looks at request l (at most 64): its length,
   // capacity and first row, all requested together with the status word.  A split is R
-  // rows, the same for every request: the batch's rows over the kv-head's `target`
-  // workgroups, no fewer than 256 rows and no less than a sixteenth of the longest
-  // request.  Request l then takes ceil(rows / R) consecutive workgroups (target + batch
-  // are launched, the ones left over have nothing to do).
+  // rows, the same for every request, and request l takes ceil(rows / R) consecutive
+  // workgroups of each kv-head.  R is about the smallest with which these are
+  // `target` (whole rounds of resident workgroups; a few more are launched, which the short
+  // last splits make room for), no fewer than 256 rows and no less than a sixteenth of the
+  // longest request.
   int first = 0, lane_ctx = 0, used = 0;
+  bool flat = false;
+  int counts = 0, call_counts = 0;   // of the request (or, flat, of the call at once), of the call
   if constexpr (BAL) {
     const int l = threadIdx.x % kWave, lb = min(l, batch - 1);
     const int32_t pending = __hip_atomic_load(status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -146,7 +157,7 @@ __global__ __launch_bounds__(NW * kWave, 2) void decode_kernel(
     const int64_t lo = row_off[lb];
     stop = stops(pending);
     const bool fits = ll >= 0 && ll < lc && ll < max_ctx;   // (behind an error a length may be anything)
-    if (__any(!fits) && blockIdx.x == 0 && kvh == 0 && threadIdx.x == 0) raise_status(status, SONIC_ERR_CAPACITY);
+    if (__any(!fits) && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) raise_status(status, SONIC_ERR_CAPACITY);
     lane_ctx = l < batch && fits ? ll + 1 : 0;
     const int groups = (lane_ctx + kGroupRows - 1) / kGroupRows;
     const int total = __builtin_amdgcn_readlane(wave_scan(groups), kWave - 1);
@@ -155,13 +166,42 @@ __global__ __launch_bounds__(NW * kWave, 2) void decode_kernel(
     for (int o = 8; o > 0; o >>= 1) longest = max(longest, __shfl_xor(longest, o));
     longest = max(max(__builtin_amdgcn_readlane(longest, 0), __builtin_amdgcn_readlane(longest, 16)),
                   max(__builtin_amdgcn_readlane(longest, 32), __builtin_amdgcn_readlane(longest, 48)));
-    const int rg = max(max(256 / kGroupRows, (longest + kMaxSplits - 1) / kMaxSplits), (total + target - 1) / target);
-    const int mine = (groups + rg - 1) / rg;
-    const int upto = wave_scan(mine);
-    used = __builtin_amdgcn_readlane(upto, kWave - 1);
-    const int w = blockIdx.x;
+    const unsigned ug = groups;
+    const int active = __popcll(__ballot(lane_ctx > 0));
+    int rg = max(max(256 / kGroupRows, (longest + kMaxSplits - 1) / kMaxSplits), (total + target - 1) / target);
+    int mine, upto;
+    auto cut = [&](int groups_each) {
+      rg = groups_each;
+      mine = (ug + rg - 1) / static_cast<unsigned>(rg);
+      upto = wave_scan(mine);
+      used = __builtin_amdgcn_readlane(upto, kWave - 1);
+    };
+    cut(rg);
+    if (used > nsplit) {
+      // a request's last split is half full on average: go on there, and end where every
+      // request may have an empty one
+      const int half = max(rg, (2 * total - 1) / (2 * target - active) + 1);
+      int most = longest;
+      if (nsplit > active) most = min(most, (total + nsplit - active - 1) / (nsplit - active));
+#pragma unroll 1
+      for (int i = 0; used > nsplit; ++i) cut(i < 4 ? min(most, half + half * i / 32) : most);
+    }
+    const int w = heads_first ? blockIdx.y : blockIdx.x;
     b = __popcll(__ballot(upto <= w));
     R = rg * kGroupRows;
+    // The workgroups left without rows count for the active requests in turn, or, where there
+    // are few of them, everything counts for the call at once: one level of counts less at
+    // the call's end (0.8 us of 30), but a thousand in one word take 10 us.
+    const unsigned spare = nsplit - used;
+    flat = spare * Hkv <= 128;
+    if (active == 0) return;   // no request has room: nothing to count or advance
+    counts = Hkv * (active + static_cast<int>(spare));
+    int rank = 0, expect = 0;
+    if (!flat) {
+      const unsigned each = spare / active, more = spare - each * active;
+      rank = lanes_below(__ballot(lane_ctx > 0));
+      expect = Hkv * (1 + each + (rank < more ? 1 : 0));
+    }
     if (w < used) {
       nsp = __builtin_amdgcn_readlane(mine, b);
       first = __builtin_amdgcn_readlane(upto, b) - nsp;
@@ -170,9 +210,16 @@ __global__ __launch_bounds__(NW * kWave, 2) void decode_kernel(
       const uint32_t hi32 = __builtin_amdgcn_readlane(static_cast<int>(lo >> 32), b);
       base = static_cast<int64_t>((static_cast<uint64_t>(hi32) << 32) | lo32);
     } else {
-      b = 0, nsp = 0, first = w, len = 0, base = 0;
+      b = 0;
+      if (!flat) {
+        const int nth = (w - used) % active;
+        b = __builtin_ctzll(__ballot(lane_ctx > 0 && rank == nth));
+      }
+      nsp = 0, first = w, len = 0, base = 0;
     }
     split = w - first;
+    if (!flat) counts = __builtin_amdgcn_readlane(expect, b);
+    call_counts = active;
   } else {
     split = blockIdx.x;
     b = blockIdx.z;
@@ -200,26 +247,35 @@ __global__ __launch_bounds__(NW * kWave, 2) void decode_kernel(
   const size_t slot0 = BAL ? static_cast<size_t>(kvh) * nsplit + first : static_cast<size_t>(pair) * nsplit_max;
   float *const acc_rec = ws.part + slot0 * (G * D);
   float *const stat_rec = ws.part + static_cast<size_t>(gridDim.x) * gridDim.y * gridDim.z * (G * D) + slot0 * (2 * G);
-  // BAL: a pair's last workgroup, and every workgroup without rows, counts once in done[0];
-  // the last of the call advances every length.  A workgroup has read the lengths before
-  // it counts, so none can still see an advanced one.
-  const int all = BAL ? Hkv * (__popcll(__ballot(lane_ctx > 0)) + nsplit - used) : Hkv;
-  auto add_one = [&](int32_t *counter, bool stopped) {
+  // A pair's last workgroup counts the pair for its request in done[b]; the last pair of a
+  // request advances its length.  BAL: a workgroup without rows counts for a request as well,
+  // and a request's last count is one count of the call in the upper bits of done[0]; the
+  // last of the call advances every length.  A workgroup has read the lengths before it
+  // counts, so none can still see an advanced one.
+  constexpr int kCallOne = 1 << 16, kLowBits = kCallOne - 1;
+  auto add = [&](int32_t *counter, int n, bool stopped) {
     if (stopped) __hip_atomic_fetch_or(counter, kStopBit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    return __hip_atomic_fetch_add(counter, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return __hip_atomic_fetch_add(counter, n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   };
-  auto count = [&](bool stopped) { return add_one(&ws.done[BAL ? 0 : b], stopped); };
+  auto count = [&](bool stopped) { return add(&ws.done[BAL && flat ? 0 : b], 1, stopped); };
   auto advance = [&](int old) {   // the first wave; `old` is its first lane's
     old = __builtin_amdgcn_readfirstlane(old);
-    if ((old & ~kStopBit) != all - 1) return;
-    if ((old & kStopBit) == 0) {
-      if (BAL) {
-        if (lane_ctx > 0) cache_len[threadIdx.x] = lane_ctx;
-      } else if (threadIdx.x == 0) {
-        cache_len[b] = n_ctx;
+    if constexpr (BAL) {
+      if ((old & kLowBits) != counts - 1) return;
+      if (!flat) {
+        if (threadIdx.x == 0) old = add(&ws.done[0], kCallOne, (old & kStopBit) != 0);
+        old = __builtin_amdgcn_readfirstlane(old);
+        if ((old & ~kStopBit) >> 16 != call_counts - 1) return;
+      }
+      if ((old & kStopBit) == 0 && lane_ctx > 0) cache_len[threadIdx.x] = lane_ctx;
+      if (threadIdx.x < batch) ws.done[threadIdx.x] = 0;
+    } else {
+      if ((old & ~kStopBit) != Hkv - 1) return;
+      if (threadIdx.x == 0) {
+        if ((old & kStopBit) == 0) cache_len[b] = n_ctx;
+        ws.done[b] = 0;
       }
     }
-    if (threadIdx.x == 0) ws.done[BAL ? 0 : b] = 0;
   };
   if (lane == 0) s_stop[wave] = stop;
   auto any_stop = [&]() {   // behind a barrier
@@ -260,7 +316,7 @@ __global__ __launch_bounds__(NW * kWave, 2) void decode_kernel(
   // while the partials load; the last pair of a request advances the length.
   auto finish_pair = [&](bool stopped) {
     if (threadIdx.x == 0) {
-      const int old = add_one(&ws.arrive[pair], stopped);
+      const int old = add(&ws.arrive[pair], 1, stopped);
       s_last = (old & ~kStopBit) == (BAL ? nsp : nsplit) - 1 ? ((old & kStopBit) != 0 ? 2 : 1) : 0;
     }
     __syncthreads();
@@ -580,16 +636,15 @@ __global__ __launch_bounds__(NW * kWave, 2) void decode_kernel(
   }
 }
 
-// Splits per (request, kv-head).  A workgroup fills a CU (one per CU), so with fewer
-// than 256 pairs the grid takes as many splits as keep every workgroup resident at
-// once (a 257th would wait for a whole workgroup to finish: on the 8B-shaped batch,
-// 64 pairs, 4 splits take 13.7 us per call and 5 take 18.3), each of at least 256
-// rows, and at most 16 (the merging split loads sixteen partials per memory round
-// trip; on the long-dialogue shape, 16 pairs of ~8k rows, 8 splits take 19.0 us per
-// call and 16 take 18.5, 22.6 against 24.6 us with the caches cold).  With 256 pairs
-// or more, one split, or three when the longest context reaches 2048 rows, so that
-// the longest pairs do not outlast the rest of the call when lengths are uneven
-// (dynamic-budget batch: 1 split 127.7 us, 2 117.1, 3 111.4, 4 121.3 per call).
+// Splits per (request, kv-head).  With fewer than 256 pairs the grid takes as many splits
+// as give every CU a workgroup (64 pairs of 1.3k rows: 4 splits took 13.7 us per call and 5
+// took 18.3, with eight waves a workgroup), each of at least 256 rows, and at most 16 (the
+// merging split loads sixteen partials per memory round trip; 16 pairs of ~8k rows: 8 splits
+// took 19.0 us per call and 16 took 18.5, 22.6 against 24.6 us with the caches cold).  With
+// 256 pairs or more, unless the rows are shared (see decode_shape), one split, or three when
+// the longest context reaches 2048 rows, so that the longest pairs do not outlast the rest
+// of the call when lengths are uneven (512 pairs of 180 .. 4,300 rows: 1 split took 127.7
+// us, 2 117.1, 3 111.4, 4 121.3 per call).
 static int decode_splits(int batch, int Hkv, int max_ctx) {
   const long pairs = static_cast<long>(batch) * Hkv;
   if (pairs >= 256) return max_ctx >= 2048 ? 3 : 1;
@@ -608,34 +663,34 @@ DecodeShape decode_shape(int batch, int Hkv, int G, int D, int max_ctx, bool mas
   // what a call needs, however it is cut: a smaller workspace is refused
   const size_t least = sh.splits > 1 ? part(pairs * sh.splits) : 0;
   // Evenly shared rows (see the kernel) where a call fills the GPU several times over and
-  // contexts may be long and uneven.  512 four-wave workgroups are resident; a request's
-  // last split is half empty on average, so `target` aims at whole rounds of 512 with
-  // half a split per pair to spare: 64 contexts of 180 .. 4300 rows, 8 kv-heads, 83.8 us
-  // with three splits per pair, 80.0 so (two rounds aimed at; 90 with one); 32 contexts of
-  // 375 .. 8192 rows 90.9 and 80.7.  Fewer pairs keep a split per pair and range: there
-  // the plan and the count over the whole call cost 2.4 us of 12 and evenness gains less.
-  if (!masked && batch <= kWave && pairs >= 256 && max_ctx >= 2048) {
-    long rounds = 2;
-    while (512 * rounds - pairs / 2 < pairs) ++rounds;
-    const long target = (512 * rounds - pairs / 2 + Hkv - 1) / Hkv;
-    if (std::max(least, part((target + batch) * Hkv)) <= part_bytes) {
+  // contexts may be long and uneven.  512 four-wave workgroups are resident, `target` is whole
+  // rounds of them: two for 256 pairs, a round more for every 256 pairs (half as many again
+  // where contexts may pass 6k rows: a finer cut costs 2 us of 14 with short ranges and gains
+  // 10 of 260 with long ones).  Measured against three splits a pair, 32 / 8 heads: 64 contexts
+  // of 100 .. 4,000 rows 51.8 us and 58.7, 32 of 100 .. 8,000 47.3 and 51.7, 64 of 4,000 195
+  // and 197, 64 of 100 (under a bound of 8,192) 17.2 and 20.5.  From 1,024 pairs on three
+  // splits do as well or better (16 / 16 heads, 64 of 100 .. 4,000 rows 117 and, shared, 145).
+  // Fewer than 256 pairs keep a split per pair and range: there the plan and the count over
+  // the whole call cost 2.4 us of 12 and evenness gains less.
+  if (!masked && batch <= kWave && pairs >= 256 && pairs < 1024 && max_ctx >= 2048) {
+    const long rounds = std::max(2L, max_ctx < 6144 ? (pairs + 255) / 256 : (3 * pairs + 511) / 512);
+    const long target = 512 * rounds / Hkv, launched = target + (batch + 15) / 16;
+    if (std::max(least, part(launched * Hkv)) <= part_bytes) {
       sh.target = static_cast<int>(target);
-      sh.splits = static_cast<int>(target + batch);
+      sh.splits = static_cast<int>(launched);
     }
   }
   const long slots = sh.target > 0 ? static_cast<long>(sh.splits) * Hkv : pairs * sh.splits;
   sh.part_bytes = std::max(least, sh.target > 0 ? part(slots) : 0);
-  // Four waves, two workgroups per CU, where there are enough workgroups: one starts and
-  // merges while the other streams (512 pairs of 200 rows 13.7 us with four, 18.1 with
-  // eight), and with one workgroup per CU and short ranges, where starting and merging
-  // are most of the call (64 pairs of 1.3k rows in four ranges each 12.1 and 13.0).  With
-  // fewer workgroups, or long ranges on one per CU, eight keep more loads in flight
-  // (8 pairs of 8k rows 11.8, with four 13.0; 400 pairs of 80 .. 1900 rows 28.0 and
-  // 33.0), as where the second round of 512 would be at most half full (768 workgroups of
-  // 1.5k rows: 118.6, with four 121.8).  D = 64 fits twice with eight (64 pairs of 4k rows
-  // 13.0, with four 13.4).
-  // Up to 256 rows a range, four waves also merge and start sooner: 64 pairs of 64 rows 5.1
-  // us with four, 5.5 with eight; 88 pairs of up to 289 rows 8.7 and 8.3.
+  // Four waves, two workgroups per CU, or eight, one per CU.  Of two workgroups one starts and
+  // merges while the other streams; eight waves keep more loads in flight where a CU has one
+  // workgroup, and even out contexts of uneven length.  D = 128, 32 / 8 heads, four and eight
+  // waves: 512 pairs of 200 rows 13.7 and 18.1 us, 64 of 1.3k rows in four ranges each 12.1 and
+  // 13.0, 64 of 64 rows 5.1 and 5.5; 8 pairs of 8k rows 13.0 and 11.8, 400 of 80 .. 1,900 rows
+  // 33.0 and 28.0.  Between 256 and 768 workgroups equal contexts would gain from four (400
+  // pairs of 500 rows 21.7 and 24.6, 576 of 1,000 55.1 and 60.6) what uneven ones lose, so
+  // four are taken there only for short ranges and where one round of 512 is nearly full.
+  // D = 64 fits twice on a CU with eight (64 pairs of 4k rows 13.0, with four 13.4).
   const bool tiny = max_ctx <= 256L * sh.splits;
   const bool two = (slots >= 480 && slots <= 512) || slots > 768;
   const bool brief = slots >= 256 && slots < 480 && max_ctx <= 512L * sh.splits;
@@ -673,7 +728,7 @@ static void launch_decode_dg(int batch, int Hkv, int max_ctx, const DecodeShape 
                              const int64_t *row_off, const int32_t *row_cap, int32_t *cache_len,
                              const uint8_t *row_role, const uint16_t *q, const uint16_t *k_new, const uint16_t *v_new,
                              float scale_log2, float *out, DecodeWs ws, int32_t *status, hipStream_t stream) {
-  const dim3 grid(sh.splits, Hkv, sh.target > 0 ? 1 : batch);
+  const dim3 grid = sh.target > 0 && Hkv * D * 2 >= kLongRow ? dim3(Hkv, sh.splits) : dim3(sh.splits, Hkv, sh.target > 0 ? 1 : batch);
 #define GO(MASKED, NW, BAL)                                                                                  \
   decode_kernel<D, G, MASKED, NW, BAL><<<grid, dim3(NW * kWave), 0, stream>>>(                               \
       kc, vc, row_off, row_cap, cache_len, row_role, q, k_new, v_new, out, ws, status, Hkv, sh.splits, max_ctx, \

@@ -375,3 +375,53 @@ def test_decode_infinite_values(B, Hq, Hkv, d, lens, max_ctx):
         ok = np.isfinite(want)
         assert np.array_equal(got[b][~ok], want[~ok]), f"request {b}"
         assert np.abs(got[b][ok] - want[ok]).max() <= 1e-4, f"request {b}"   # as in test_decode_work_split
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,d,lens,max_ctx", [
+    (64, 8, 4, 64, (100, 3, 40), 8192),              # far more workgroups launched than have rows
+    (16, 16, 16, 128, (2500, 40, 3000, 700), 3600),  # long cache rows: the kv-heads alternate
+    (8, 64, 64, 64, (17, 1500, 300), 2048),
+    (64, 32, 8, 64, (1900, 60, 500, 1300), 2048),    # more requests' remainders than workgroups to spare
+    (33, 24, 8, 128, (4096, 16, 2), 4200),
+    (64, 16, 16, 64, (30, 2100), 2200)])             # 1,024 pairs: three splits each
+@pytest.mark.parametrize("how", ["workspace", "smallest workspace", "no workspace", "all full"])
+def test_decode_shared_rows(B, Hq, Hkv, d, lens, max_ctx, how):
+    """256 pairs and more: rows shared over the batch, or, in a workspace that has no room for
+    that, three splits a pair; on the library's own array; and with no request that has room."""
+    H.need_gpu()
+    rng = np.random.default_rng(B + Hq + d)
+    lens = np.array([lens[b % len(lens)] for b in range(B)], np.int64)
+    cache, k, v = plain_caches(rng, lens, 2, Hkv, d)
+    if how == "all full":
+        cache.row_cap.copy_(cache.length)
+    off = cache.row_off_host
+    status = torch.zeros(1, dtype=torch.int32, device="cuda")
+    counters = -(-B * 4 // 256) * 256 + -(-B * Hq * 4 // 256) * 256
+    n = counters + B * Hq * 3 * (d + 2) * 4 if how == "smallest workspace" else sonic.decode_workspace_bytes(B, Hq, d, max_ctx)
+    ws = torch.zeros(n, dtype=torch.uint8, device="cuda")
+    out = torch.full((B, Hq, d), 7.0, dtype=torch.float32, device="cuda")
+    check = sorted({0, 1, 2, 3, B - 1})
+    for t in range(2):
+        q, kn, vn = (W.f32_to_bf16_bits(rng.standard_normal((B, h, d)).astype(np.float32)) for h in (Hq, Hkv, Hkv))
+        args = (cache.k, cache.v, cache.row_off, cache.row_cap, cache.length, bf16_to_device(q), bf16_to_device(kn),
+                bf16_to_device(vn), out)
+        st = (sonic.compressed_decode_noalloc(*args, status, max_ctx) if how == "no workspace" else
+              sonic.compressed_decode(*args, ws, status, max_ctx))
+        assert st == sonic.OK
+        torch.cuda.synchronize()
+        assert not bool(ws[:-(-B * 4 // 256) * 256 + 4 * B * Hkv].any())   # the counters
+        if how == "all full":
+            assert int(status.item()) == sonic.ERR_CAPACITY and bool((out == 7.0).all())
+            assert np.array_equal(cache.length.cpu().numpy(), lens)
+            continue
+        assert int(status.item()) == 0
+        got, gk = out.cpu().numpy(), bf16_to_host(cache.k)
+        for b in range(B):
+            o, ln = int(off[b]), int(lens[b])
+            if b in check:
+                want = OD.decode_step(q[b], k[o:o + ln], v[o:o + ln], kn[b], vn[b])
+                assert np.abs(got[b] - want).max() <= 1e-4, f"request {b} step {t}"   # as in test_decode_work_split
+            k[o + ln], v[o + ln] = kn[b], vn[b]
+            assert np.array_equal(gk[o + ln], kn[b])
+            lens[b] += 1
+        assert np.array_equal(cache.length.cpu().numpy(), lens)

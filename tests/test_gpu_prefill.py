@@ -6,6 +6,7 @@ import torch
 import workloads as W
 from oracle import mask as OM
 from paper_2601_21927_amd import sonic
+from paper_2601_21927_amd.runner import bf16_to_device
 from tests import gpu_helpers as H
 
 pytestmark = pytest.mark.gpu
@@ -260,3 +261,33 @@ def test_prefill_row_blocks(Hq, Hkv, d):
     rows = [np.arange(lay.length) for lay in lays]
     for b, want in enumerate(H.oracle_prefill_rows(batch, rows)):
         H.assert_close(got[int(batch.cu_seqlens[b]) + rows[b]], want, f"request {b}")
+
+
+@pytest.mark.parametrize("Hq,Hkv,d,stats", [(2, 2, 128, False), (3, 3, 64, True), (4, 2, 64, False), (2, 1, 128, True)])
+def test_prefill_row_blocks_leave_out_later_values(Hq, Hkv, d, stats):
+    """Infinite and NaN values of a later 32-row block of a run stay out of the rows of the
+    blocks before it, which do not see them."""
+    H.need_gpu()
+    lays = [W.RequestLayout(0, [], [], 200), W.RequestLayout(100, [150], [5], 40), W.RequestLayout(70, [130, 97], [33, 2], 128)]
+    batch = W.make_batch("later", lays, Hq, Hkv, d, seed=Hq + d)
+    db = H.device_batch(batch)
+    mass = torch.empty((batch.total_tokens, Hq), dtype=torch.float32, device="cuda") if stats else None
+    assert db.prefill(nexus_mass=mass) == sonic.OK
+    torch.cuda.synchronize()
+    clean = db.out.clone()
+    bad = batch.v.copy()
+    first_bad = []
+    for b, lay in enumerate(lays):
+        s, runs = int(batch.cu_seqlens[b]), H.run_starts(lay) + [lay.length]
+        start, end = max(zip(runs, runs[1:]), key=lambda r: r[1] - r[0])   # the longest run's last rows
+        at = start + (end - start - 1) // 32 * 32
+        bad[s + at:s + end:2], bad[s + at + 1:s + end:2] = 0x7F80, 0x7FC0
+        first_bad.append((start, at))
+    db.v.copy_(bf16_to_device(bad))
+    db.out.fill_(7.0)
+    assert db.prefill(nexus_mass=mass) == sonic.OK
+    torch.cuda.synchronize()
+    assert db.read_status() == 0
+    for b, (start, at) in enumerate(first_bad):
+        s = int(batch.cu_seqlens[b])
+        assert torch.equal(db.out[s + start:s + at], clean[s + start:s + at]), f"request {b}"

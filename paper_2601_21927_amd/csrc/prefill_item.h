@@ -38,6 +38,10 @@ const char *vreq = uniform_ptr(reinterpret_cast<const char *>(rows.seg_v + head0
 const char *kpre = uniform_ptr(reinterpret_cast<const char *>(rows.pre_k + phead0));
 const char *vpre = uniform_ptr(reinterpret_cast<const char *>(rows.pre_v + phead0));
 
+// RB > 1: a wave whose block lies past the end of a short run only stages, which leaves the LDS
+// and the matrix cores to the others (8,000 runs of 3 rows, one q-head of 64: 1,385 us without)
+const bool rowless = RB > 1 && row_blk >= t.nrows;
+
 const int nchunks = (nv + kKeyChunk - 1) / kKeyChunk;
 // this group's steps: [c_first, c_first + nloc); loads for steps past them
 // (the pipeline runs two ahead) fetch a step past the list end instead
@@ -95,6 +99,12 @@ auto step = [&](int c, uint16_t *kc_lds, const uint16_t *vc_lds, uint16_t *vn_ld
   lds_barrier();                                   // K(c) in LDS; every wave is past P.V(c - 1)
   stage_v(c + 1, vn_lds);
   const int vk0 = c * kKeyChunk;
+  if (rowless) {
+    wait_vm<2 * NJ>();
+    lds_barrier();
+    stage_k(c + 2, kc_lds);
+    return;
+  }
 
   // ---- S^T = K . Q^T for two 32-key blocks ----
   f32x16 sacc[2];

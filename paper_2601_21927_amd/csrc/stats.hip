@@ -114,8 +114,8 @@ __global__ __launch_bounds__(G * kWave, 3) void key_weight_kernel(const int32_t 
         if (valid) w = *reinterpret_cast<const u32x4 *>(q + qidx * D + 16 * ds + 8 * g);
         qf[ds] = __builtin_bit_cast(bf16x8, w);
       }
-      const float lse = valid ? ws.lse[qidx] : INFINITY;
-      const int lim = npre + r + 1 - j0 - 4 * g;   // bound on the element's key, less j0 + 4 g
+      const float lse = ws.lse[qidx];   // (a row past the last: the first one's, not used)
+      const int lim = valid ? npre + r + 1 - j0 - 4 * g : 0;   // bound on the element's key, less j0 + 4 g
 #pragma unroll
       for (int kb = 0; kb < 2; ++kb) {
         f32x16 s = f32x16{};
@@ -126,9 +126,8 @@ __global__ __launch_bounds__(G * kWave, 3) void key_weight_kernel(const int32_t 
           s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, qf[ds], s, 0, 0, 0);
         }
         // Element e holds key 8 * (e / 4) + 4 * g + e % 4 of the 32-key block, row r.  A
-        // row sees the keys below npre + r + 1; one past the last has an infinite
-        // normaliser, its terms are zero.  So one comparison with a constant per element
-        // stands for the row's, the key's and the causal test.
+        // row sees the keys below npre + r + 1, one past the last sees none.  So one comparison
+        // with a constant per element stands for the row's, the key's and the causal test.
 #pragma unroll
         for (int e = 0; e < 16; ++e) {
           const bool vis = kb * 32 + 8 * (e >> 2) + (e & 3) < lim;

@@ -120,3 +120,23 @@ def test_stats_workload_rows():
         close(mass[s + rows], OS.nexus_mass(*args, rows=rows), f"workload 2 A_nexus req {b}")
         close(weight[s:e], OS.key_weight(*args), f"workload 2 w(x) req {b}")
         assert np.all(weight[s:e][batch.role[s:e] == OL.HISTORY_TEXT] == 0)
+
+
+@pytest.mark.parametrize("Hq,Hkv,d", [(8, 2, 128), (2, 2, 64)])
+def test_stats_key_with_an_infinite_element(Hq, Hkv, d):
+    """A key that every current row scores -inf gets weight 0, whatever the number of current
+    rows (the rows that fill up the last block of 32 have no query)."""
+    lays = [W.RequestLayout(6, [40], [5], 33), W.RequestLayout(3, [], [], 70)]
+    batch = W.make_batch("kinf", lays, Hq, Hkv, d, seed=29)
+    q, k = batch.q.copy(), batch.k.copy()
+    q[:, :, 0] = 0x3F80                        # every query's first element is 1
+    bad = [int(batch.cu_seqlens[b]) + lay.length - 9 for b, lay in enumerate(lays)]
+    k[bad, :, 0] = 0xFF80
+    batch.q, batch.k = q, k
+    _, mass, weight = run_stats(batch)
+    assert np.array_equal(weight[bad], np.zeros(len(bad), np.float32))
+    assert np.all(np.isfinite(weight)) and np.all(np.isfinite(mass))
+    k2 = k.copy()
+    k2[bad, :, 0] = W.f32_to_bf16_bits(np.full(1, -1e30, np.float32))[0]   # the oracle's -inf: no weight either
+    batch.k = k2
+    check_batch(batch, sonic.NEXUS_ALL, mass, weight)

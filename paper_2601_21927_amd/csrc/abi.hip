@@ -414,6 +414,9 @@ int32_t sonic_nexus_extend(int32_t batch, int32_t total_new, int32_t Hq, int32_t
     // groups of one workgroup instead.
     const int64_t item_bound = (static_cast<int64_t>(total_new + kTileRows - 1) / kTileRows + batch) * Hkv;
     const int ks = (G <= 4 && item_bound <= 2 * static_cast<int64_t>(di->num_cus)) ? 2 : 1;
+    // (One and two q-heads without the split run single blocks on the grid of the row blocks'
+    // kernel, fewer workgroups than would fit: 4 x 600 new rows, 16 / 16 heads of 64, took 124.5
+    // us so and 128.6 with all that fit; 8 x 300 rows, 8 / 8 and 32 / 32 of 128, the same.)
     int grid = di->num_cus * (ks == 2 ? di->prefill_ks2_blocks[d == 128][G] : di->prefill_blocks[0][d == 128][G]);
     grid = (grid + kNumXcd - 1) / kNumXcd * kNumXcd;
     AttnRows rows{nexus_cu, cache_row_off, static_cast<const uint16_t *>(q), static_cast<const uint16_t *>(k),

@@ -331,3 +331,17 @@ def test_extend_with_a_pending_layout_error_writes_nothing():
     assert np.array_equal(bf16_to_host(case.kc), kc0) and np.array_equal(bf16_to_host(case.vc), vc0)
     assert np.array_equal(case.length.cpu().numpy(), len0)
     assert torch.all(case.out == 7.0)
+
+
+@pytest.mark.parametrize("Hq,Hkv,d", [(16, 16, 128), (32, 16, 64), (16, 16, 64), (32, 16, 128)])
+def test_extend_many_new_rows_one_and_two_heads(Hq, Hkv, d):
+    """One and two q-heads per kv-head with more work items than twice the CUs: single blocks,
+    no key split."""
+    H.need_gpu()
+    lays = [W.RequestLayout(40, [100, 300], [20, 290], 0), W.RequestLayout(3, [350], [333], 0),
+            W.RequestLayout(17, [30, 212], [5, 298], 0), W.RequestLayout(0, [320], [299], 0)]
+    # counted as the library does: blocks of 32 rows over the batch, plus one per request
+    new = sum(lay.nexus[-1] for lay in lays)
+    assert (-(-new // 32) + len(lays)) * Hkv > 2 * torch.cuda.get_device_properties(0).multi_processor_count
+    batch = W.make_batch("ext-heads", lays, Hq, Hkv, d, seed=31 + Hq + d)
+    check_case(ExtendCase(batch), "many rows")

@@ -470,10 +470,14 @@ static void launch_tiles(int T, int K, int N, const uint8_t *role, const uint16_
 hipError_t launch_routed_gemm(int T, int K, int N, const uint8_t *role, const uint16_t *x, const uint16_t *w_text,
                               const uint16_t *w_nexus, float *y, int32_t *blk_nexus, int32_t *counts, int32_t *perm,
                               int32_t *status, hipStream_t stream) {
-  // The weight-streaming kernel reads the weights once per 128 rows, the tiles spread them
-  // over fewer workgroups: 256 rows of K = 4096 take 22.0 us streamed and 22.5 tiled for
-  // N = 4096, 39 and 28 for N = 6144; 128 rows 20.5 and 20.9, N = 6144.
-  if (T <= kSkinnyRows && (T <= 128 || N <= 4096)) {
+  // The weight-streaming kernel stages its block of x rows once per 32 columns and weight
+  // set, so the rows it multiplies, in whole blocks, times the columns bound its use: in
+  // us, weights not in the Infinity Cache, no Nexus rows / a fifth of them, streamed against
+  // tiled, K = 4096: 64 rows of N = 14336 41 / 70 and 42 / 56; of 28672 72 / 125 and 58 / 98;
+  // 128 rows of N = 6144 29 / 51 and 33 / 40, of 10240 52 / 76 and 39 / 48, of 14336 55 / 100
+  // and 51 / 60.  (128 x 256 tiles behind routing kernels took 72 / 76 and 75 / 85 for the last two.)
+  const int blocks = T <= 16 ? 16 : T <= 32 ? 32 : T <= 64 ? 64 : T <= 128 ? 128 : 256;
+  if (T <= 16 || (T <= kSkinnyRows && static_cast<int64_t>(blocks) * N <= (1 << 20))) {
 #define SKINNY(NT, TT, NW, S)                                                                               \
   skinny_proj_kernel<NT, TT, NW, S>                                                                         \
       <<<dim3((N + 16 * NT - 1) / (16 * NT), 2, (T + 16 * TT - 1) / (16 * TT)), dim3(NW * kWave), 0, stream>>>( \
@@ -497,15 +501,6 @@ hipError_t launch_routed_gemm(int T, int K, int N, const uint8_t *role, const ui
 #undef SKINNY
     return hipGetLastError();
   }
-  const bool local = T <= kLocalRows;
-  if (!local) {
-    const int nblk = (T + kRouteThreads - 1) / kRouteThreads;
-    route_count_kernel<<<dim3(nblk), dim3(kRouteThreads), 0, stream>>>(role, T, blk_nexus);
-    route_scan_kernel<<<dim3(1), dim3(kRouteThreads), 0, stream>>>(nblk, T, blk_nexus, counts, status);
-    route_fill_kernel<<<dim3(nblk), dim3(kRouteThreads), 0, stream>>>(role, T, blk_nexus, counts, perm);
-    const hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-  }
 #define TILES(PM, PN, S)                                                                                        \
   (local ? launch_tiles<PM, PN, S, true>(T, K, N, role, x, w_text, w_nexus, y, counts, perm, status, stream)    \
          : launch_tiles<PM, PN, S, false>(T, K, N, role, x, w_text, w_nexus, y, counts, perm, status, stream))
@@ -513,18 +508,33 @@ hipError_t launch_routed_gemm(int T, int K, int N, const uint8_t *role, const ui
   // with less waste.  A shape's cost is its time for one tile per CU (measured, K = 4096:
   // 256 x 256 93 us, 128 x 256 58, 128 x 128 36, 64 x 128 43 for two, 64 x 64 29 for two
   // and 20 alone) times the rounds it takes; a last, partial round runs faster than a
-  // full one and counts half its missing part.  Best against 256 x 256, K = 4096: T = 512,
+  // full one and counts half its missing part.  Over 950 sizes (130 .. 9,000 rows, K = 256 ..
+  // 14336, N = 200 .. 28672) the shape so chosen takes 3 % more than the best one on average
+  // and up to a half more where the estimate of the last round is off.  Best against 256 x 256, K = 4096: T = 512,
   // N = 6144 37.9 us (128 x 128) and 94.6; T = 1024, N = 1024 21.5 (64 x 64) and 91.0;
   // T = 4096, N = 6144 256 x 256 itself, 207 against 245 for 128 x 256.
   const struct { int pm, pn, cost, least; } shapes[] = {
-      {256, 256, 100, 100}, {128, 256, 60, 60}, {128, 128, 38, 38}, {64, 128, 24, 24}, {64, 64, 15, 20}};
+      {256, 256, 100, 100}, {128, 256, 60, 60}, {128, 128, 39, 39}, {64, 128, 24, 24}, {64, 64, 15, 20}};
   int best = 0;
-  double best_cost = 0;
+  double best_cost = 0, best_rounds = 0;
   for (int i = 0; i < 5; ++i) {
     const double tiles = ((T + shapes[i].pm - 1) / shapes[i].pm + 1.0) * ((N + shapes[i].pn - 1) / shapes[i].pn);
     const double rounds = std::max(1.0, tiles / 256);
     const double cost = std::max<double>(shapes[i].least, 0.5 * (rounds + std::ceil(rounds)) * shapes[i].cost);
-    if (i == 0 || cost < best_cost) best = i, best_cost = cost;
+    if (i == 0 || cost < best_cost) best = i, best_cost = cost, best_rounds = rounds;
+  }
+  // Routing inside the tiles costs each of the tiles a CU does in turn about 0.7 us and 0.3 per
+  // 1,024 rows (the two smallest shapes are two at a time), the routing kernels 4 to 5 us:
+  // T = 5000, N = 28672, K = 64 146 us inside and 135 by kernels, T = 4000, N = 8192, K = 4096 285
+  // and 271; T = 700, N = 28672, K = 64 27.9 and 29.4, T = 4000, N = 1024, K = 256 13.4 and 17.6.
+  const bool local = T <= kLocalRows && best_rounds / (best >= 3 ? 2 : 1) * (0.7 + T * 0.0003) <= 4.5;
+  if (!local) {
+    const int nblk = (T + kRouteThreads - 1) / kRouteThreads;
+    route_count_kernel<<<dim3(nblk), dim3(kRouteThreads), 0, stream>>>(role, T, blk_nexus);
+    route_scan_kernel<<<dim3(1), dim3(kRouteThreads), 0, stream>>>(nblk, T, blk_nexus, counts, status);
+    route_fill_kernel<<<dim3(nblk), dim3(kRouteThreads), 0, stream>>>(role, T, blk_nexus, counts, perm);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
   }
   switch (best) {
     case 0: TILES(256, 256, 2); break;

@@ -193,3 +193,15 @@ def test_projection_status_changes_while_it_runs(T, K, N):
         assert bool((left | (y == want)).all()), f"call {i}"
         if T > 8192:   # one workgroup decides for the whole call
             assert bool(left.all()) or not bool(left.any()), f"call {i}"
+
+
+@pytest.mark.parametrize("T,K,N", [(17, 64, 32768), (32, 128, 32769), (64, 64, 16385), (65, 192, 8192), (128, 64, 8193),
+                                   (16, 64, 70000), (4000, 64, 6144), (3000, 128, 10240), (7000, 64, 1030)])
+def test_projection_wide_outputs(T, K, N):
+    """Either side of the bound on rows times columns between the weight-streaming kernel and
+    the tiles, and of the choice between routing inside the tiles and by kernels."""
+    rng = np.random.default_rng(7 * T + K + N)
+    x, wt, wn = _bits(rng, (T, K)), _bits(rng, (N, K), 0.05), _bits(rng, (N, K), 0.05)
+    role = np.where(np.arange(T) % 5 < 1, OL.NEXUS, OL.CURRENT).astype(np.uint8)
+    rows = np.unique(np.concatenate([[0, T - 1], rng.integers(0, T, 60)]))
+    check(run(role, x, wt, wn), role, x, wt, wn, f"T={T} K={K} N={N}", rows)

@@ -30,13 +30,11 @@ hipError_t launch_plan_extend(int batch, int total_new, int max_rows, const int3
                               const int32_t *row_cap, PrefillWs ws, int32_t *status, hipStream_t stream);
 hipError_t launch_extend_stage(int batch, int max_rows, int Hkv, int D, const int32_t *keep_len,
                                const int32_t *body_len, const uint16_t *kc, const uint16_t *vc, const int64_t *row_off,
-                               PrefillWs ws, uint16_t *k_stage, uint16_t *v_stage, const int32_t *status,
-                               hipStream_t stream);
+                               PrefillWs ws, uint16_t *k_stage, uint16_t *v_stage, hipStream_t stream);
 hipError_t launch_extend_append(int batch, int max_new, int max_rows, int Hkv, int D, const int32_t *nexus_cu,
                                 const int32_t *keep_len, uint16_t *kc, uint16_t *vc, const int64_t *row_off,
                                 int32_t *cache_len, const uint16_t *k_new, const uint16_t *v_new, PrefillWs ws,
-                                const uint16_t *k_stage, const uint16_t *v_stage, const int32_t *status,
-                                hipStream_t stream);
+                                const uint16_t *k_stage, const uint16_t *v_stage, hipStream_t stream);
 hipError_t launch_prefill(int D, int G, int grid, bool stats, int ks, int tile_rows, AttnRows rows, PrefillWs ws, int Hkv, float scale_log2,
                           hipStream_t stream);
 hipError_t launch_compact(int batch, int total_tokens, int max_seqlen, int Hkv, int D, const int32_t *cu,
@@ -404,8 +402,7 @@ int32_t sonic_nexus_extend(int32_t batch, int32_t total_new, int32_t Hq, int32_t
   if (body_len != nullptr) {
     // the tail rows after the body, staged before the cache update moves them
     e = launch_extend_stage(batch, max_rows, Hkv, d, keep_len, body_len, static_cast<const uint16_t *>(k_cache),
-                            static_cast<const uint16_t *>(v_cache), cache_row_off, ws, k_stage, v_stage, dev_status,
-                            stream);
+                            static_cast<const uint16_t *>(v_cache), cache_row_off, ws, k_stage, v_stage, stream);
     if (e != hipSuccess) return SONIC_ERR_HIP;
   }
   if (total_new > 0) {
@@ -428,8 +425,7 @@ int32_t sonic_nexus_extend(int32_t batch, int32_t total_new, int32_t Hq, int32_t
   e = launch_extend_append(batch, total_new, max_rows, Hkv, d, nexus_cu, keep_len, static_cast<uint16_t *>(k_cache),
                            static_cast<uint16_t *>(v_cache), cache_row_off, cache_len,
                            static_cast<const uint16_t *>(k), static_cast<const uint16_t *>(v), ws,
-                           body_len != nullptr ? k_stage : nullptr, body_len != nullptr ? v_stage : nullptr,
-                           dev_status, stream);
+                           body_len != nullptr ? k_stage : nullptr, body_len != nullptr ? v_stage : nullptr, stream);
   return finish(e, dev_status, stream);
 }
 

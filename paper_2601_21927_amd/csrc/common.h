@@ -197,7 +197,8 @@ struct PrefillWs {
   uint16_t *k_pre;     // [T, Hkv, D] prefix copies of K and V, request b's rows at offset cu[b]
   uint16_t *v_pre;
   int32_t *ctrl;       // [16] ctrl[0] = number of descriptors, ctrl[1] = number of key blocks of
-                       //      the key-weight pass, ctrl[8 + x] = queue head of XCD x
+                       //      the key-weight pass, ctrl[2] = the call's outputs are to be written
+                       //      (key weights, next-turn step), ctrl[8 + x] = queue head of XCD x
   // attention statistics (used only when they are asked for)
   float *lse;          // [T, Hq] log2-domain softmax normaliser of every row and q-head
   float *wpart;        // [Hkv, T] key weight of every kept key, one partial per kv-head

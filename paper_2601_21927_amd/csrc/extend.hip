@@ -67,7 +67,9 @@ __global__ __launch_bounds__(kExtendThreads) void plan_extend_kernel(
   __shared__ int s_ok;
   const int b = blockIdx.x;
   if (b == 0 && threadIdx.x < kNumXcd) ws.ctrl[8 + threadIdx.x] = 0;   // the work queues
-  const bool clear = block_status_clear(status, &s_ok);
+  // workgroup 0's look at the status word decides for the whole call: the word may change at
+  // any time, and the step is done for every request or for none
+  const bool clear = b != 0 || block_status_clear(status, &s_ok);
   ExtendReq own;
   const int own_code = extend_check(b, nexus_cu, keep_len, body_len, cache_len, row_cap, max_rows, total_new, &own);
   int before = 0, all = 0, nbad = 0;
@@ -84,15 +86,12 @@ __global__ __launch_bounds__(kExtendThreads) void plan_extend_kernel(
     all += total[1];
     nbad += total[2];
   }
-  if (own_code != 0 && clear && threadIdx.x == 0) raise_status(status, own_code);
-  if (!clear || nbad > 0) {
-    if (threadIdx.x == 0) {
-      if (b == 0) ws.ctrl[0] = 0;
-      ws.req[b] = ReqInfo{0, 0, 0, 0, 0, 0};
-    }
-    return;
+  if (own_code != 0 && threadIdx.x == 0) raise_status(status, own_code);   // (a pending error stays)
+  if (b == 0 && threadIdx.x == 0) {
+    ws.ctrl[0] = clear && nbad == 0 ? all : 0;
+    ws.ctrl[2] = clear && nbad == 0 ? 1 : 0;
   }
-  if (b == 0 && threadIdx.x == 0) ws.ctrl[0] = all;
+  if (nbad > 0) return;
   const int s = nexus_cu[b];
   const int keep = keep_len[b];
   const int body = cache_len[b] - keep - own.rest;
@@ -118,9 +117,8 @@ __global__ __launch_bounds__(kExtendThreads) void plan_extend_kernel(
 __global__ __launch_bounds__(kExtendThreads) void extend_stage_kernel(
     const int32_t *__restrict__ keep_len, const int32_t *__restrict__ body_len, const uint16_t *__restrict__ kc,
     const uint16_t *__restrict__ vc, const int64_t *__restrict__ row_off, PrefillWs ws, uint16_t *__restrict__ k_stage,
-    uint16_t *__restrict__ v_stage, int max_rows, int row_pieces, const int32_t *status) {
-  __shared__ int s_ok;
-  if (!block_status_clear(status, &s_ok)) return;
+    uint16_t *__restrict__ v_stage, int max_rows, int row_pieces) {
+  if (ws.ctrl[2] == 0) return;
   const int b = blockIdx.y;
   const int rest = ws.req[b].nruns;
   const size_t src0 = static_cast<size_t>(row_off[b] + keep_len[b] + body_len[b]) * row_pieces;
@@ -141,10 +139,8 @@ __global__ __launch_bounds__(kExtendThreads) void extend_append_kernel(
     const int32_t *__restrict__ nexus_cu, const int32_t *__restrict__ keep_len, uint16_t *__restrict__ kc,
     uint16_t *__restrict__ vc, const int64_t *__restrict__ row_off, int32_t *__restrict__ cache_len,
     const uint16_t *__restrict__ k_new, const uint16_t *__restrict__ v_new, PrefillWs ws,
-    const uint16_t *__restrict__ k_stage, const uint16_t *__restrict__ v_stage, int max_rows, int row_pieces,
-    const int32_t *status) {
-  __shared__ int s_ok;
-  if (!block_status_clear(status, &s_ok)) return;
+    const uint16_t *__restrict__ k_stage, const uint16_t *__restrict__ v_stage, int max_rows, int row_pieces) {
+  if (ws.ctrl[2] == 0) return;
   const int b = blockIdx.y;
   const int s = nexus_cu[b];
   const int kn = nexus_cu[b + 1] - s;
@@ -185,24 +181,21 @@ static unsigned extend_chunks(long rows, int row_pieces) {
 
 hipError_t launch_extend_stage(int batch, int max_rows, int Hkv, int D, const int32_t *keep_len,
                                const int32_t *body_len, const uint16_t *kc, const uint16_t *vc, const int64_t *row_off,
-                               PrefillWs ws, uint16_t *k_stage, uint16_t *v_stage, const int32_t *status,
-                               hipStream_t stream) {
+                               PrefillWs ws, uint16_t *k_stage, uint16_t *v_stage, hipStream_t stream) {
   const int row_pieces = Hkv * D / 8;
   extend_stage_kernel<<<dim3(extend_chunks(max_rows, row_pieces), batch), dim3(kExtendThreads), 0, stream>>>(
-      keep_len, body_len, kc, vc, row_off, ws, k_stage, v_stage, max_rows, row_pieces, status);
+      keep_len, body_len, kc, vc, row_off, ws, k_stage, v_stage, max_rows, row_pieces);
   return hipGetLastError();
 }
 
 hipError_t launch_extend_append(int batch, int max_new, int max_rows, int Hkv, int D, const int32_t *nexus_cu,
                                 const int32_t *keep_len, uint16_t *kc, uint16_t *vc, const int64_t *row_off,
                                 int32_t *cache_len, const uint16_t *k_new, const uint16_t *v_new, PrefillWs ws,
-                                const uint16_t *k_stage, const uint16_t *v_stage, const int32_t *status,
-                                hipStream_t stream) {
+                                const uint16_t *k_stage, const uint16_t *v_stage, hipStream_t stream) {
   const int row_pieces = Hkv * D / 8;
   const long rows = static_cast<long>(max_new) + (k_stage != nullptr ? max_rows : 0);
   extend_append_kernel<<<dim3(extend_chunks(rows, row_pieces), batch), dim3(kExtendThreads), 0, stream>>>(
-      nexus_cu, keep_len, kc, vc, row_off, cache_len, k_new, v_new, ws, k_stage, v_stage, max_rows, row_pieces,
-      status);
+      nexus_cu, keep_len, kc, vc, row_off, cache_len, k_new, v_new, ws, k_stage, v_stage, max_rows, row_pieces);
   return hipGetLastError();
 }
 

@@ -256,16 +256,12 @@ __global__ __launch_bounds__(kPlanThreads) void plan_runs_kernel(const int32_t *
 // its first slot in `order`.  Requests run by decreasing total cost (ties by
 // index), so that first slot is the number of descriptors of the requests ranked
 // before it: a workgroup sum over the batch, no global sort.  Workgroup 0 also
-// writes the descriptor count and resets the queues.
+// writes the descriptor count (`ok`: 0 where it found an error pending) and resets the queues.
 __device__ __forceinline__ void plan_order(int b, bool ok, int batch, const int32_t *__restrict__ cu, const PrefillWs &ws,
                                            int *hist, int *lds) {
   static_assert(kCostBuckets == kPlanThreads, "one histogram bucket per thread");
   hist[threadIdx.x] = 0;
   if (b == 0 && threadIdx.x < kNumXcd) ws.ctrl[8 + threadIdx.x] = 0;
-  if (!ok) {
-    if (b == 0 && threadIdx.x == 0) ws.ctrl[0] = 0;
-    return;
-  }
   const int64_t cb = ws.req[b].cost;
   int before = 0, all = 0;
   for (int j0 = 0; j0 < batch; j0 += kPlanThreads) {
@@ -282,7 +278,7 @@ __device__ __forceinline__ void plan_order(int b, bool ok, int batch, const int3
     before += total[0];
     all += total[1];
   }
-  if (b == 0 && threadIdx.x == 0) ws.ctrl[0] = all;
+  if (b == 0 && threadIdx.x == 0) ws.ctrl[0] = ok ? all : 0;
   const int nt = ws.req[b].ntiles;
   const int base = cu[b];
   const int dst = before;
@@ -361,7 +357,8 @@ __device__ __forceinline__ void gather_prefix(int b, int bx, int gx, const int32
 
 // Both need only the run kernel's results: workgroups [0, batch) order a request's
 // descriptors, the others copy prefixes (one launch after the other, the order took 6 us
-// of its own before a copy of 19).
+// of its own before a copy of 19).  Only workgroup 0 looks at the status word, which may change
+// at any time: where it gives a descriptor count, every slot below it has to be filled.
 __global__ __launch_bounds__(kPlanThreads) void plan_finish_kernel(int batch, const int32_t *__restrict__ cu,
                                                                    const uint16_t *__restrict__ k,
                                                                    const uint16_t *__restrict__ v, PrefillWs ws,
@@ -369,10 +366,10 @@ __global__ __launch_bounds__(kPlanThreads) void plan_finish_kernel(int batch, co
   __shared__ int hist[kCostBuckets];
   __shared__ int lds[2 * (kPlanThreads / kWave)];
   __shared__ int s_ok;
-  const bool ok = block_status_clear(status, &s_ok);
+  const bool ok = blockIdx.x != 0 || block_status_clear(status, &s_ok);
   const int w = static_cast<int>(blockIdx.x) - batch;
   if (w < 0) plan_order(blockIdx.x, ok, batch, cu, ws, hist, lds);
-  else if (ok) gather_prefix(w / gx, w % gx, gx, cu, k, v, ws, row_pieces);
+  else gather_prefix(w / gx, w % gx, gx, cu, k, v, ws, row_pieces);
 }
 
 // Grammar check and run table only (ws.req, ws.prefix_pos, ws.runs; ws.tiles is

@@ -45,8 +45,6 @@ __global__ __launch_bounds__(256) void recon_items_kernel(int batch, int max_row
   __shared__ int s_y[256];        // prefix rows (system + Nexus) before each run
   __shared__ int s_nx[256];       // run is a Nexus run
   __shared__ int s_red[2][256 / kWave];
-  __shared__ int s_ok;
-  const bool clear = block_status_clear(status, &s_ok);
   const int b = blockIdx.x;
   int before = 0, total = 0;
   for (int i = threadIdx.x; i < batch; i += 256) {
@@ -72,11 +70,14 @@ __global__ __launch_bounds__(256) void recon_items_kernel(int batch, int max_row
     before += s_red[1][w];
   }
   const bool fits = total <= max_rows;
+  // This look at the status word is the call's only one: the word may change at any time, and
+  // where a total is given every item below it has to be listed.
   if (b == 0 && threadIdx.x == 0) {
-    if (clear && !fits) raise_status(status, SONIC_ERR_CAPACITY);
+    const bool clear = __hip_atomic_load(status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0;
+    if (!fits) raise_status(status, SONIC_ERR_CAPACITY);   // (an error that is pending stays)
     ws.ctrl[0] = (clear && fits) ? total : 0;
   }
-  if (!clear || !fits) return;
+  if (!fits) return;
   const int s0 = cu[b];
   const int L = cu[b + 1] - s0;
   const ReqInfo ri = ws.req[b];

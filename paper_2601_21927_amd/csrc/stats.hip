@@ -31,7 +31,8 @@ __global__ __launch_bounds__(kStatThreads) void stats_plan_kernel(int batch, con
                                                                   const int32_t *status) {
   __shared__ int lds[kStatThreads / kWave + 1];
   __shared__ int s_ok;
-  const bool ok = block_status_clear(status, &s_ok);
+  // (no descriptors: the prefill was stopped, whatever the status word is by now)
+  const bool ok = block_status_clear(status, &s_ok) && ws.ctrl[0] > 0;
   int carry = 0;
   for (int base = 0; base < batch; base += kStatThreads) {
     const int b = base + threadIdx.x;
@@ -52,7 +53,10 @@ __global__ __launch_bounds__(kStatThreads) void stats_plan_kernel(int batch, con
     for (int j = 0; j < nblk; ++j) ws.kblocks[carry + off + j] = make_int2(b, j);
     carry += tot;
   }
-  if (threadIdx.x == 0) ws.ctrl[1] = carry;
+  if (threadIdx.x == 0) {
+    ws.ctrl[1] = carry;
+    ws.ctrl[2] = ok ? 1 : 0;
+  }
 }
 
 template <int D> __device__ __forceinline__ int swz_w(int m) { return m & (D / 8 - 1); }
@@ -183,10 +187,8 @@ __global__ __launch_bounds__(G * kWave, 3) void key_weight_kernel(const int32_t 
 
 // w[x] = (sum over kv-heads of the partials) / Hq for kept keys, 0 for body keys.
 __global__ __launch_bounds__(256) void key_weight_sum_kernel(const uint8_t *__restrict__ role, PrefillWs ws,
-                                                             int Hkv, int Hq, int T, float *__restrict__ w,
-                                                             const int32_t *status) {
-  __shared__ int s_ok;
-  if (!block_status_clear(status, &s_ok)) return;
+                                                             int Hkv, int Hq, int T, float *__restrict__ w) {
+  if (ws.ctrl[2] == 0) return;
   for (int x = blockIdx.x * 256 + threadIdx.x; x < T; x += gridDim.x * 256) {
     float v = 0.f;
     if (role[x] != kText)
@@ -239,8 +241,7 @@ hipError_t launch_key_weight(int batch, int T, int Hq, int Hkv, int D, int num_c
   long blocks = (static_cast<long>(T) + 255) / 256;
   if (blocks > 4L * num_cus) blocks = 4L * num_cus;
   if (blocks < 1) blocks = 1;
-  key_weight_sum_kernel<<<dim3(static_cast<unsigned>(blocks)), dim3(256), 0, stream>>>(role, ws, Hkv, Hq, T, w,
-                                                                                        status);
+  key_weight_sum_kernel<<<dim3(static_cast<unsigned>(blocks)), dim3(256), 0, stream>>>(role, ws, Hkv, Hq, T, w);
   return hipGetLastError();
 }
 

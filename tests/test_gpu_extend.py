@@ -345,3 +345,47 @@ def test_extend_many_new_rows_one_and_two_heads(Hq, Hkv, d):
     assert (-(-new // 32) + len(lays)) * Hkv > 2 * torch.cuda.get_device_properties(0).multi_processor_count
     batch = W.make_batch("ext-heads", lays, Hq, Hkv, d, seed=31 + Hq + d)
     check_case(ExtendCase(batch), "many rows")
+
+
+def test_extend_status_changes_while_it_runs():
+    """Another stream raises and clears the status word while steps run: a step is done for every
+    request, or for none."""
+    H.need_gpu()
+    rng = np.random.default_rng(51)
+    lays = _ending_layouts(rng, 8, max_h=3, max_b=100, max_k=50, max_s=60)
+    batch = W.make_batch("flips", lays, 8, 2, 64, seed=51)
+    case = ExtendCase(batch)
+    body = torch.from_numpy(((case.len0 - np.array(case.keep)) // 2).astype(np.int32)).cuda()   # rows stay behind it
+    cap = case.len0 + case.kn
+    case.cap, case.off = cap, np.concatenate([[0], np.cumsum(cap)[:-1]])
+    case.row_off.copy_(torch.from_numpy(case.off))
+    case.row_cap.copy_(torch.from_numpy(cap.astype(np.int32)))
+    k0 = torch.randn((int(cap.sum()), 2, 64), device="cuda").to(torch.bfloat16)
+    len0 = case.length.clone()
+    ws = torch.empty(sonic.nexus_extend_workspace_bytes(batch.batch, len(case.q), int(cap.max()), 2, 64), dtype=torch.uint8,
+                     device="cuda")
+
+    def step():
+        kc, vc, length, out = k0.clone(), k0.clone(), len0.clone(), torch.full_like(case.out, 7.0)
+        assert sonic.nexus_extend(case.nexus_cu, case.keep_len, kc, vc, case.row_off, case.row_cap, length, case.q, case.k,
+                                  case.v, out, ws, case.status, max_rows=int(cap.max()), body_len=body) == sonic.OK
+        return kc, vc, length, out
+    want = step()
+    torch.cuda.synchronize()
+    assert int(case.status.item()) == 0 and not torch.equal(want[2], len0)
+    untouched = (k0, k0, len0, torch.full_like(case.out, 7.0))
+    flips = H.Flips(case.status, sonic.ERR_BAD_LAYOUT)
+    got = []
+    for i in range(24):
+        if i % 4 == 0:
+            flips.start()
+        got.append(step())
+    torch.cuda.synchronize()
+    done = 0
+    for i, g in enumerate(got):
+        same = all(torch.equal(a.view(torch.int16) if a.dtype == torch.bfloat16 else a,
+                               b.view(torch.int16) if b.dtype == torch.bfloat16 else b) for a, b in zip(g, want))
+        none = all(torch.equal(a, b) for a, b in zip(g, untouched))
+        assert same or none, i
+        done += same
+    H.note(f"  steps done: {done} of {len(got)}")

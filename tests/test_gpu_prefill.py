@@ -291,3 +291,32 @@ def test_prefill_row_blocks_leave_out_later_values(Hq, Hkv, d, stats):
     for b, (start, at) in enumerate(first_bad):
         s = int(batch.cu_seqlens[b])
         assert torch.equal(db.out[s + start:s + at], clean[s + start:s + at]), f"request {b}"
+
+
+@pytest.mark.parametrize("Hq,Hkv", [(8, 2), (2, 2)])
+def test_prefill_status_changes_while_it_runs(Hq, Hkv):
+    """Another stream raises and clears the status word while calls run: a call's outputs are
+    all written, and right, or all left alone."""
+    H.need_gpu()
+    lays = [W.RequestLayout(30, [100, 40], [20, 33], 50)] * 6 + [W.RequestLayout(3, [9], [1], 400)]
+    batch = W.make_batch("flips", lays, Hq, Hkv, 64, seed=23)
+    db = H.device_batch(batch)
+    T = batch.total_tokens
+    new = lambda *s: torch.full(s, float("nan"), dtype=torch.float32, device="cuda")
+    outs = [(new(T, Hq, 64), new(T, Hq), new(T)) for _ in range(25)]
+    flips = None
+    for i, (out, mass, weight) in enumerate(outs):   # the first one undisturbed
+        if i % 4 == 1:
+            flips = flips or H.Flips(db.status, sonic.ERR_BAD_LAYOUT)
+            flips.start()
+        db.out = out
+        assert db.prefill(nexus_mass=mass, key_weight=weight) == sonic.OK
+    torch.cuda.synchronize()
+    left = 0
+    for i, got in enumerate(outs):
+        for j, (x, want) in enumerate(zip(got, outs[0])):
+            none = bool(torch.isnan(x).all())
+            left += none
+            assert torch.equal(x, want) or (none and i > 0), (i, j)
+        assert torch.equal(torch.isnan(got[0]).any(), torch.isnan(got[1]).any()), i
+    H.note(f"  outputs left alone: {left} of {3 * len(outs)}")

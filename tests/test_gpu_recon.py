@@ -103,3 +103,30 @@ def test_recon_is_reproducible_and_workload_shaped():
     wt, wc, wr = OR.recon_request(h[cu[0]:cu[1]], role[cu[0]:cu[1]], turn[cu[0]:cu[1]])
     idx = np.unique(np.concatenate([[0, len(wc) - 1], rng.integers(0, len(wc), 40)]))
     check((t[idx], c[idx], r[idx]), (wt[idx], wc[idx], wr[idx]), "8B request 0")
+
+
+def test_recon_status_changes_while_it_runs():
+    """Another stream raises and clears the status word while calls run: a call's outputs are
+    all written, and right, or all left alone."""
+    H.need_gpu()
+    rng = np.random.default_rng(1850)
+    lays = [W.RequestLayout(3, [70, 20, 9], [7, 5, 2], 1)] * 9
+    Dm = 256
+    h, role, turn, cu, t, c, r, st = run(lays, Dm, rng)
+    assert st == 0
+    n = len(c)
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    args = (dev(cu), dev(role), dev(turn), bf16_to_device(h))
+    ws = torch.empty(sonic.nexus_recon_workspace_bytes(len(lays), len(role)), dtype=torch.uint8, device="cuda")
+    status = torch.zeros(1, dtype=torch.int32, device="cuda")
+    flips = H.Flips(status, sonic.ERR_BAD_LAYOUT)
+    new = lambda *s: torch.full(s, float("nan"), dtype=torch.float32, device="cuda")
+    outs = [(new(n, Dm), new(n), new(n)) for _ in range(32)]
+    for i, o in enumerate(outs):
+        if i % 8 == 0:
+            flips.start()
+        assert sonic.nexus_recon_targets(*args, *o, ws, status) == sonic.OK
+    torch.cuda.synchronize()
+    for i, o in enumerate(outs):
+        got = [x.cpu().numpy() for x in o]
+        assert all(np.array_equal(g, w) for g, w in zip(got, (t, c, r))) or all(np.isnan(g).all() for g in got), i

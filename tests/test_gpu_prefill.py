@@ -5,6 +5,7 @@ import torch
 
 import workloads as W
 from oracle import mask as OM
+from oracle import stats as OS
 from paper_2601_21927_amd import sonic
 from paper_2601_21927_amd.runner import bf16_to_device
 from tests import gpu_helpers as H
@@ -259,8 +260,13 @@ def test_prefill_row_blocks(Hq, Hkv, d):
     assert db.read_status() == 0 and torch.equal(plain, db.out)
     got = plain.cpu().numpy()
     rows = [np.arange(lay.length) for lay in lays]
+    got_mass = mass.cpu().numpy()
     for b, want in enumerate(H.oracle_prefill_rows(batch, rows)):
-        H.assert_close(got[int(batch.cu_seqlens[b]) + rows[b]], want, f"request {b}")
+        s, e = int(batch.cu_seqlens[b]), int(batch.cu_seqlens[b + 1])
+        H.assert_close(got[s + rows[b]], want, f"request {b}")
+        want = OS.nexus_mass(batch.q[s:e], batch.k[s:e], batch.role[s:e], batch.turn_id[s:e])
+        # sums of fp32 probabilities from exact products, as in the statistics tests
+        assert np.all(np.abs(got_mass[s:e] - want) <= 1e-5 + 1e-4 * np.abs(want)), f"request {b}: Nexus mass"
 
 
 @pytest.mark.parametrize("Hq,Hkv,d,stats", [(2, 2, 128, False), (3, 3, 64, True), (4, 2, 64, False), (2, 1, 128, True)])

@@ -140,3 +140,15 @@ def test_stats_key_with_an_infinite_element(Hq, Hkv, d):
     k2[bad, :, 0] = W.f32_to_bf16_bits(np.full(1, -1e30, np.float32))[0]   # the oracle's -inf: no weight either
     batch.k = k2
     check_batch(batch, sonic.NEXUS_ALL, mass, weight)
+
+
+@pytest.mark.parametrize("Hq,Hkv,d,scope", [(2, 2, 128, sonic.NEXUS_ALL), (3, 3, 64, sonic.NEXUS_UP_TO_OWN),
+                                             (4, 2, 128, sonic.NEXUS_UP_TO_OWN), (2, 1, 64, sonic.NEXUS_ALL)])
+def test_stats_row_blocks(Hq, Hkv, d, scope):
+    """One and two q-heads per kv-head: several 32-row blocks of a run in one workgroup, each
+    with its rows' masses and normalisers; runs longer than a workgroup's rows."""
+    lays = [W.RequestLayout(140, [150, 33], [65, 2], 260), W.RequestLayout(0, [300], [40], 129),
+            W.RequestLayout(5, [], [], 97)]
+    batch = W.make_batch("stats-blocks", lays, Hq, Hkv, d, seed=900 + Hq + d)
+    _, mass, weight = run_stats(batch, scope)
+    check_batch(batch, scope, mass, weight)

@@ -1,6 +1,6 @@
 // Decode over the retained context {I_sys, N, Q_n} (problem statement).
 //
-// decode_kernel: grid (split, kv-head, request), 8 waves.  A split owns a
+// decode_kernel: grid (split, kv-head, request), four or eight waves.  A split owns a
 // contiguous range of the request's context rows 0..len (row len is the token
 // being generated: it is read from k_new/v_new, and split 0 of each kv-head also
 // appends it to the cache).  The range is cut into 16-row groups, dealt to the
@@ -9,10 +9,11 @@
 //            column c < G is q-head kvh*G + c;
 //   softmax  per q-head, online, fp32, exp2 with log2(e) folded into the scale;
 //            a column's statistics live in the four lanes that hold it;
-//   values   O^T (d x 16 cols) += V^T . P^T   v_mfma_f32_16x16x16_bf16, V read
+//   values   O^T (d x 16 cols) += V^T . P^T   v_mfma_f32_16x16x32_bf16, V read
 //            back transposed (ds_read_b64_tr_b16); P^T is the score accumulator
-//            itself, rounded to bf16 (its lane layout is the operand layout), and
-//            the softmax sum adds those rounded values.
+//            itself (its lane layout is the operand layout) as the sum of two bf16
+//            values, the 16 rows' first and second parts in one product against
+//            the rows of V twice, and the softmax sum adds those values.
 // K and V rows go straight from global memory to a two-slot LDS ring of the
 // wave's own (direct-to-LDS loads), so a wave keeps its next group in flight
 // while it computes one.  The waves then merge through LDS.
@@ -446,8 +447,8 @@ __global__ __launch_bounds__(NW * kWave, 2) void decode_kernel(
   auto vptr = [&](int r) { return r < len ? vbase + static_cast<size_t>(r) * row_stride : vnew; };
   uint16_t *my_ring = ring + wave * 4 * SLOT;
 
-  // Group g of the split covers rows r_begin + 16 g ...; wave w takes groups w, w + 8,
-  // w + 16, ... (a fixed order, so the result does not depend on timing).
+  // Group g of the split covers rows r_begin + 16 g ...; wave w takes groups w, w + NW,
+  // w + 2 NW, ... (a fixed order, so the result does not depend on timing).
   auto group_row0 = [&](int g) { return r_begin + kGroupRows * g; };
   // issue the loads of group g into ring slot s: lane -> (row, 16-byte position) of
   // each instruction's rows; the position holds the row's swizzled chunk

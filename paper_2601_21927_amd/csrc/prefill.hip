@@ -1,8 +1,9 @@
 // Masked prefill attention (Sec. 3.2) on gfx950 matrix cores.
 //
 // Work item = (descriptor, kv-head).  A workgroup holds G waves, one per q-head
-// of the kv-head's group, so every K/V block staged in LDS serves G heads.
-// Each wave owns the 32 query rows of its descriptor for one q-head and walks
+// of the kv-head's group, so every K/V block staged in LDS serves G heads (for one
+// and two q-heads, G waves per 32-row block of a descriptor of four and two blocks).
+// Each wave owns 32 query rows of its descriptor for one q-head and walks
 // the descriptor's visible keys in steps of 64:
 //
 //   S^T (64 keys x 32 rows)   = K . Q^T   v_mfma_f32_32x32x16_bf16, fp32 accumulate
@@ -14,9 +15,9 @@
 // (lane % 32) in every accumulator, so row maxima and sums need a single
 // cross-lane exchange (lane ^ 32) and rescaling needs no exchange at all.
 //
-// Only the last one or two 64-key steps of a descriptor can hold masked
-// entries (the ragged end of the key list and the causal diagonal); all
-// earlier steps are fully visible and skip the predicate.
+// Only the last one or two 64-key steps of a descriptor (three with several
+// blocks) can hold masked entries (the ragged end of the key list and the causal
+// diagonal); all earlier steps are fully visible and skip the predicate.
 //
 // LDS is double-buffered: while step c is computed, the K and V rows of step
 // c+1 stream straight into the other buffer (global_load_lds_dwordx4, no

@@ -16,7 +16,9 @@
 // v_mfma_f32_16x16x32_bf16, K in steps of 64.  Both operands are K-contiguous rows (x
 // rows and weight rows), staged straight from global memory into an LDS ring of S steps
 // (direct-to-LDS loads).  LDS rows are 128 bytes with an XOR swizzle on the 16-byte
-// chunk index, so the fragment reads (16 rows at one chunk) are bank-conflict free.
+// chunk index, which spreads 16 rows at one chunk over all banks; a fragment read takes
+// four chunks at once, and the counters still show it at two passes instead of one
+// (SQ_LDS_BANK_CONFLICT half of SQ_LDS_IDX_ACTIVE).
 // Tiles are laid out so that the workgroups of one XCD share a band of output columns
 // and walk its row tiles in order: the x rows a tile needs are also needed by the tiles
 // of the other columns of the band, resident on the same XCD at the same time, and so is
@@ -135,10 +137,11 @@ __device__ __forceinline__ bool local_routes(const uint8_t *__restrict__ role, i
   return true;
 }
 
-// The matrix cores bound a large tile (T = 43392, K = 4096, N = 6144: 1.82 ms, 1.20
-// PFLOP/s, where 128 x 256 tiles with two barriers a step took 2.19 ms), the LDS reads
-// come next: a 128 x 64 part per wave reads 0.75 KB of fragments per 32 Kflop product, a
-// 64 x 64 one 1 KB, which is all the LDS delivers in that time.  Blocks of 16 x 16 keep
+// The matrix cores (58 % busy) and the LDS reads with their conflicts bound a large tile
+// (T = 43392, K = 4096, N = 6144: 1.83 ms, 1.19 PFLOP/s, where 128 x 256 tiles with two
+// barriers a step took 2.19 ms): a 128 x 64 part per wave reads 0.75 KB of fragments per
+// 32 Kflop product, a 64 x 64 one 1 KB, which at 128 B a cycle is all the LDS delivers in
+// that time even without conflicts.  Blocks of 16 x 16 keep
 // the accumulators in four-register groups; 32 x 32 blocks of this part spilled.  A small
 // tile is bound by the latency of its steps (about 1.5 us each with one in flight), so
 // its ring is deeper.

@@ -68,7 +68,14 @@ __global__ __launch_bounds__(kPlanThreads) void plan_runs_kernel(const int32_t *
   if (threadIdx.x == 0) s_cost = 0ull;
   const int s = cu[b];
   const int e = cu[b + 1];
-  if (s < 0 || e < s || e > total_tokens) {   // cu_seqlens itself is malformed
+  // cu_seqlens itself is malformed: requests may overlap, in the caller's arrays and in the
+  // workspace, so none of them is planned (every wave looks at all of it)
+  int malformed = 0;
+  for (int i = threadIdx.x % kWave; i < static_cast<int>(gridDim.x); i += kWave) {
+    const int si = cu[i], ei = cu[i + 1];
+    malformed |= si < 0 || ei < si || ei > total_tokens;
+  }
+  if (__any(malformed)) {
     if (threadIdx.x == 0) {
       raise_status(status, SONIC_ERR_BAD_LAYOUT);
       ws.req[b] = ReqInfo{0, 0, 0, 0, 0, 0};

@@ -159,6 +159,28 @@ def test_prefill_bad_layout_reports_and_leaves_output():
     assert torch.all(db.out == 7.0)
 
 
+@pytest.mark.parametrize("stats", [False, True])
+def test_prefill_overlapping_requests_are_not_planned(stats):
+    """cu_seqlens that runs backwards: requests 0 and 2 are the same rows.  Neither is planned:
+    two requests' tables and prefix copies in one place of the workspace would hold positions of
+    either.  Only the requests' (empty) records and the counts change in the workspace."""
+    H.need_gpu()
+    batch = W.make_batch("overlap", [W.RequestLayout(9, [70, 40, 33], [11, 8, 5], 20)], 4, 2, 64, seed=2)
+    T = int(batch.cu_seqlens[-1])
+    batch.cu_seqlens = np.array([0, T, 0, T], np.int32)
+    db = H.device_batch(batch)
+    db.out.fill_(7.0)
+    mass = torch.full((T, 4), 7.0, device="cuda") if stats else None
+    weight = torch.full((T,), 7.0, device="cuda") if stats else None
+    db.prefill_ws.fill_(0xAB)
+    assert db.prefill(nexus_mass=mass, key_weight=weight) == sonic.OK
+    torch.cuda.synchronize()
+    assert db.read_status() == sonic.ERR_BAD_LAYOUT
+    for x in (db.out, mass, weight):
+        assert x is None or torch.all(x == 7.0)
+    assert int((db.prefill_ws != 0xAB).sum()) <= 512
+
+
 def test_prefill_argument_errors():
     H.need_gpu()
     batch = W.make_batch("args", [W.RequestLayout(2, [3], [1], 2)], 4, 2, 64, seed=1)

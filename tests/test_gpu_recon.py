@@ -130,3 +130,22 @@ def test_recon_status_changes_while_it_runs():
     for i, o in enumerate(outs):
         got = [x.cpu().numpy() for x in o]
         assert all(np.array_equal(g, w) for g, w in zip(got, (t, c, r))) or all(np.isnan(g).all() for g in got), i
+
+
+def test_recon_overlapping_requests_are_not_listed():
+    """cu_seqlens that runs backwards (requests 0 and 2 are the same rows): no request's runs or
+    items are listed, only the empty records and the counts change in the workspace."""
+    H.need_gpu()
+    rng = np.random.default_rng(1860)
+    role, turn, cu = W.pack_layouts([W.RequestLayout(3, [70, 20, 9], [7, 5, 2], 1)])
+    T, n, Dm = len(role), 28, 64
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    ws = torch.full((sonic.nexus_recon_workspace_bytes(3, T),), 0xAB, dtype=torch.uint8, device="cuda")
+    status = torch.zeros(1, dtype=torch.int32, device="cuda")
+    outs = [torch.full(s, 7.0, dtype=torch.float32, device="cuda") for s in ((n, Dm), (n,), (n,))]
+    st = sonic.nexus_recon_targets(dev(np.array([0, T, 0, T], np.int32)), dev(role), dev(turn),
+                                   bf16_to_device(_bits(rng, (T, Dm))), *outs, ws, status)
+    torch.cuda.synchronize()
+    assert st == sonic.OK and int(status.item()) == sonic.ERR_BAD_LAYOUT
+    assert all(bool((x == 7.0).all()) for x in outs)
+    assert int((ws != 0xAB).sum()) <= 512
